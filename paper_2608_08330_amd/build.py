@@ -30,6 +30,7 @@ HIP_SOURCES = [
     "executor_hip.hip",
     "kernels/pillar.hip",
     "kernels/igemm.hip",
+    "kernels/conv_slices.hip",
     "kernels/post.hip",
     "kernels/nms.hip",
     "nms_api.hip",

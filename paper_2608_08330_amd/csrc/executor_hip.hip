@@ -62,13 +62,12 @@ class HipExecutor : public Executor {
         const size_t over_cap = n_max / size_t(p.d.max_points_per_pillar + 1) + 1;
         tiles_ = int(n_tiles);
         // Kernel variant and split-K of every conv layer.
-        int n_cu = 0;
-        HIP_TRY(hipDeviceGetAttribute(&n_cu, hipDeviceAttributeMultiprocessorCount, dev_));
-        if (n_cu <= 0) n_cu = 256;
+        HIP_TRY(hipDeviceGetAttribute(&n_cu_, hipDeviceAttributeMultiprocessorCount, dev_));
+        if (n_cu_ <= 0) n_cu_ = 256;
         plans_.clear();
         size_t ws_bytes = 0;
         for (const ConvLayer &c : p.convs) {
-            kern::ConvPlan cp = kern::conv_plan(p.bf16, c.Hi, c.Wi, c.Ci, c.Ho, c.Wo, c.Co, c.stride, n_cu);
+            kern::ConvPlan cp = kern::conv_plan(p.bf16, c.Hi, c.Wi, c.Ci, c.Ho, c.Wo, c.Co, c.stride, n_cu_);
             if (o.conv_variant > 0)
                 cp = kern::conv_plan_forced(p.bf16, cp, o.conv_variant, o.conv_splits, c.Ci, c.Ho, c.Wo, c.Co, c.stride);
             plans_.push_back(cp);
@@ -209,6 +208,15 @@ class HipExecutor : public Executor {
                                      : static_cast<const void *>(w.mat_f32.data());
         HIP_TRY(hipMemcpy(d_mat, mat_src, mat_bytes, hipMemcpyHostToDevice));
         HIP_TRY(hipMemcpy(d_bias, w.bias.data(), p.bias_floats * 4, hipMemcpyHostToDevice));
+        // ... and in fragment order for the layers that read them so
+        d_frag_.assign(p.convs.size(), nullptr);
+        for (size_t l = 0; l < p.convs.size(); ++l) {
+            const ConvLayer &c = p.convs[l];
+            if (!plans_[l].slices) continue;
+            HIP_TRY(alloc(&d_frag_[l], size_t(9) * c.Ci * c.Co * p.elt));
+            HIP_TRY(kern::conv_frag(p.bf16, static_cast<const char *>(d_mat) + c.w_off * p.elt, d_frag_[l], c.Co, c.Ci,
+                                    join_stream_));
+        }
         HIP_TRY(hipDeviceSynchronize());
         return RTCC_OK;
     }
@@ -850,8 +858,10 @@ class HipExecutor : public Executor {
             ga.ws = ga.ws_b[0];
             // with timing, conv nodes are timed by events bracketing their
             // kernels' execution (no dispatch gap)
-            HIP_TRY(kern::conv3x3(p.bf16, ga, s, timing ? lead.kev[2 * l] : nullptr,
-                                  timing ? lead.kev[2 * l + 1] : nullptr));
+            hipEvent_t k0 = timing ? lead.kev[2 * l] : nullptr, k1 = timing ? lead.kev[2 * l + 1] : nullptr;
+            ga.wfrag = d_frag_[l];
+            ga.n_cu = n_cu_;
+            HIP_TRY(plans_[l].slices ? kern::conv_slices(p.bf16, ga, s, k0, k1) : kern::conv3x3(p.bf16, ga, s, k0, k1));
             if (timing) HIP_TRY(hipEventRecord(lead.ev[ev], s));
             ++ev;
         }
@@ -1321,6 +1331,8 @@ class HipExecutor : public Executor {
     std::vector<void *> dev_allocs_;
     void *d_mat = nullptr, *d_bias = nullptr, *d_zero = nullptr;
     std::vector<kern::ConvPlan> plans_;
+    std::vector<void *> d_frag_;  // per conv layer: weights in fragment order (null: not used)
+    int n_cu_ = 0;
     void *d_fused = nullptr, *d_head = nullptr, *d_head_counts = nullptr, *d_rec = nullptr, *d_count = nullptr;
     int nms_max_ = 0;  // 0: no NMS
     void *d_nms_rank = nullptr, *d_nms_flag = nullptr, *d_nms_order = nullptr, *d_nms_foot = nullptr;

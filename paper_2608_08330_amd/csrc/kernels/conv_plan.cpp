@@ -10,8 +10,31 @@ ConvPlan conv_plan(bool bf16, int Hi, int Wi, int Ci, int Ho, int Wo, int Co, in
     (void)Hi;
     (void)Wi;
     const int bk = bf16 ? 32 : 16;  // implicit GEMM K step (64 bytes)
-    ConvPlan p{kConvImplicit, 1, 0, kConvImplicit, 1, kConvImplicit, 1 << 30};
+    ConvPlan p{kConvImplicit, 1, 0, kConvImplicit, 1, kConvImplicit, 1 << 30, false};
     const int elt = bf16 ? 2 : 4;
+    // Layers whose tiles do not fill the chip: the K slices of a tile summed
+    // side by side in one block (conv_slices.hip has the times).  The line is
+    // where a map's 4 x 16 x 128 tiles cover half the CUs: below it the halo
+    // tiling would be split over blocks (one map of 25 x 88 x 128 -> 128 9.8
+    // against 4.8 us); above it one map gains little or nothing (100 x 140 x
+    // 128 10.7 against 10.4, 80 x 100 x 256 19.8 against 20.5) and a batch
+    // loses (four maps of 100 x 140 x 128 23.5 against 28.8).  Without a
+    // 128-channel tiling, and for the 64-channel stride-2 entries below the
+    // 256-pixel implicit GEMM's line, the alternative is the split implicit
+    // GEMM, which is slower at every size (eight maps of 128 x 180 x 64 -> 64
+    // 64 against 24 us, five of 320 x 400 x 64 -> 128 stride 2 103 against 51).
+    const int slices = conv_slices_of(Ci * elt);
+    if (slices) {
+        const int t4 = ((Wo + 15) / 16) * ((Ho + 3) / 4) * (Co / 128);
+        const bool implicit256 = ((Ho * Wo + 255) / 256) * (Co / 128) >= n_cu;
+        const bool narrow = stride == 2 && Ci * elt < 256;
+        if (Co % 128 != 0 || t4 < n_cu / 2 || (narrow && !implicit256)) {
+            p.variant = p.variant_wide = p.variant_wider = stride == 1 ? kConvHalo4 : kConvHalo4S2;
+            p.splits = slices;
+            p.slices = true;
+            return p;
+        }
+    }
     if (stride == 1 && Co % 128 == 0) {
         // 8 x 16-pixel tiles with 8 wavefronts where the grid fills the
         // chip; otherwise 4 x 16-pixel tiles with 4 wavefronts, split over
@@ -144,7 +167,7 @@ ConvPlan conv_plan_forced(bool bf16, const ConvPlan &planned, int variant, int s
         default: break;
     }
     if (!fits || steps % groups != 0 || steps / groups < 1) return planned;
-    ConvPlan p{variant, 1, 0, variant, 1, variant, 1 << 30};
+    ConvPlan p{variant, 1, 0, variant, 1, variant, 1 << 30, false};
     // a split-K slice holds whole chunks of one wave group's share; the
     // two-group tilings run unsplit
     if (splits > 1 && groups == 1 && steps % splits == 0) p.splits = splits;

@@ -52,7 +52,18 @@ struct ConvPlan {
     // wider_maps >= wide_maps.
     int variant_wider;
     int wider_maps;
+    // The K slices of a tile run side by side in one block (conv_slices)
+    // instead of in blocks of their own whose partial sums a second kernel
+    // adds: the summation order of tiling `variant` with `splits` slices, for
+    // every batch size.
+    bool slices = false;
 };
+// K slices of conv_slices for an input pixel of `row_bytes` bytes; 0: it has
+// no tile for this width.  64-byte channel chunks, one per slice, two per slice
+// at 512 bytes.
+inline int conv_slices_of(int row_bytes) {
+    return row_bytes == 128 ? 2 : row_bytes == 256 || row_bytes == 512 ? 4 : 0;
+}
 // Kernel variant and K split of one 3x3 conv layer on a GPU with n_cu CUs.
 // Only tilings with one wave group per tile are planned (a second group
 // would sum half of the K chunks apart, another accumulation order).

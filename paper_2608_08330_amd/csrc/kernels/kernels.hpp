@@ -127,6 +127,8 @@ struct GemmArgs {
     const void *in_b[16];
     void *out_b[16];
     float *ws_b[16];
+    const void *wfrag; // conv_slices: the weights in fragment order (conv_frag)
+    int32_t n_cu;      // conv_slices: compute units of the GPU
 };
 // With start / stop events, the first kernel of the convolution records
 // `start` when it begins executing and the last one `stop` when it ends
@@ -134,6 +136,13 @@ struct GemmArgs {
 hipError_t conv3x3(bool bf16, const GemmArgs &a, hipStream_t s, hipEvent_t start = nullptr,
                    hipEvent_t stop = nullptr);
 hipError_t deconv(bool bf16, const GemmArgs &a, hipStream_t s);
+// The convolution of a plan with ConvPlan::slices: the K slices of a tile side
+// by side in one block, summed there (no ws).  Needs wfrag and n_cu, and
+// splits = conv_slices_of(Ci * element size).
+hipError_t conv_slices(bool bf16, const GemmArgs &a, hipStream_t s, hipEvent_t start = nullptr,
+                       hipEvent_t stop = nullptr);
+// Bt [N][9 Ci] (N a multiple of 16) to the order conv_slices reads; as large.
+hipError_t conv_frag(bool bf16, const void *wt, void *out, int32_t N, int32_t Ci, hipStream_t s);
 
 // ------------------------------------------------------------ post-join
 struct WarpArgs {

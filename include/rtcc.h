@@ -490,7 +490,7 @@ RTCC_API rtcc_status rtcc_rotated_nms(const float *device_records, int64_t n, in
 /* rtcc_rotated_nms for callers that cannot allocate device memory (code
  * under HIP graph capture, tight serving loops, harnesses that forbid
  * hipMalloc): the same kernels and results, with the scratch in one
- * library-owned device array of fixed size (11.9 MB per GPU, held from the
+ * library-owned device array of fixed size (2.4 MB per GPU, held from the
  * first call on that GPU until the process ends).  Allocates nothing and
  * creates no stream.
  *   device_records, n, max_candidates, iou_threshold, device_out, kept: as

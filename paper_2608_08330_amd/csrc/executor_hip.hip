@@ -164,16 +164,14 @@ class HipExecutor : public Executor {
         nms_max_ = p.d.nms_max_candidates;
         if (nms_max_ > 0) {
             const size_t words = size_t(nms_max_ + 63) / 64;
-            HIP_TRY(alloc(&d_nms_rank, n_anchor_ * 4));
-            HIP_TRY(alloc(&d_nms_flag, n_anchor_ * 4));
+            HIP_TRY(alloc(&d_nms_key, n_anchor_ * 4));
             HIP_TRY(alloc(&d_nms_order, size_t(nms_max_) * 4));
             HIP_TRY(alloc(&d_nms_foot, size_t(nms_max_) * kern::kNmsFootDoubles * 8));
-            HIP_TRY(alloc(&d_nms_mask, size_t(nms_max_) * words * 8));
             HIP_TRY(alloc(&d_nms_out, size_t(nms_max_) * 9 * 4));
             HIP_TRY(alloc(&d_nms_count, 64));
             HIP_TRY(alloc(&d_nms_mask_t, size_t(nms_max_) * 8));
-            HIP_TRY(alloc(&d_nms_partial, size_t(kern::kNmsRankSplits) * n_anchor_ * 4));
-            HIP_TRY(alloc(&d_nms_colrows, kern::nms_colrows(nms_max_) * 4));
+            HIP_TRY(alloc(&d_nms_colrows, kern::nms_listed(nms_max_) * 4));
+            HIP_TRY(alloc(&d_nms_colwords, kern::nms_listed(nms_max_) * 8));
             HIP_TRY(alloc(&d_nms_colcount, words * 4));
         }
         HIP_TRY(hipHostMalloc(reinterpret_cast<void **>(&h_rec), n_anchor_ * 9 * 4, hipHostMallocDefault));
@@ -1058,6 +1056,7 @@ class HipExecutor : public Executor {
         da.ayaw1 = p.d.anchor_yaw[1];
         da.head_counts = static_cast<const int32_t *>(d_head_counts);
         da.rec = static_cast<float *>(d_rec);
+        da.key = static_cast<uint32_t *>(d_nms_key);
         da.count = static_cast<int32_t *>(d_count);
         HIP_TRY(kern::decode(da, s));
         if (timing) HIP_TRY(hipEventRecord(post_ev_[3], s));
@@ -1065,15 +1064,15 @@ class HipExecutor : public Executor {
             kern::NmsArgs na{};
             na.rec = static_cast<const float *>(d_rec);
             na.count = static_cast<const int32_t *>(d_count);
-            na.rank = static_cast<int32_t *>(d_nms_rank);
-            na.flag = static_cast<int32_t *>(d_nms_flag);
+            na.key = static_cast<const uint32_t *>(d_nms_key);
             na.order = static_cast<int32_t *>(d_nms_order);
             na.foot = static_cast<double *>(d_nms_foot);
-            na.mask = static_cast<unsigned long long *>(d_nms_mask);
             na.mask_t = static_cast<unsigned long long *>(d_nms_mask_t);
-            na.partial = static_cast<int32_t *>(d_nms_partial);
             na.colrows = static_cast<int32_t *>(d_nms_colrows);
+            na.colwords = static_cast<unsigned long long *>(d_nms_colwords);
             na.colcount = static_cast<int32_t *>(d_nms_colcount);
+            na.host = static_cast<uint32_t *>(h_export);  // the last kernel also hands the result to the host
+            na.host_first = export_first_;
             na.out = static_cast<float *>(d_nms_out);
             na.out_count = static_cast<int32_t *>(d_nms_count);
             na.iou_threshold = double(p.d.nms_iou_threshold);
@@ -1081,10 +1080,9 @@ class HipExecutor : public Executor {
             HIP_TRY(kern::rotated_nms(na, int64_t(n_anchor_), s));
         }
         if (timing) HIP_TRY(hipEventRecord(post_ev_[4], s));
-        HIP_TRY(kern::export_results(static_cast<const int32_t *>(d_count),
-                                     nms_max_ > 0 ? static_cast<const int32_t *>(d_nms_count) : nullptr,
-                                     static_cast<const float *>(nms_max_ > 0 ? d_nms_out : d_rec), export_first_,
-                                     h_export, s));
+        if (nms_max_ == 0)
+            HIP_TRY(kern::export_results(static_cast<const int32_t *>(d_count), static_cast<const float *>(d_rec),
+                                         export_first_, h_export, s));
         return RTCC_OK;
     }
 
@@ -1335,9 +1333,9 @@ class HipExecutor : public Executor {
     int n_cu_ = 0;
     void *d_fused = nullptr, *d_head = nullptr, *d_head_counts = nullptr, *d_rec = nullptr, *d_count = nullptr;
     int nms_max_ = 0;  // 0: no NMS
-    void *d_nms_rank = nullptr, *d_nms_flag = nullptr, *d_nms_order = nullptr, *d_nms_foot = nullptr;
-    void *d_nms_mask = nullptr, *d_nms_out = nullptr, *d_nms_count = nullptr;
-    void *d_nms_mask_t = nullptr, *d_nms_partial = nullptr, *d_nms_colrows = nullptr, *d_nms_colcount = nullptr;
+    void *d_nms_key = nullptr, *d_nms_order = nullptr, *d_nms_foot = nullptr, *d_nms_out = nullptr;
+    void *d_nms_count = nullptr, *d_nms_mask_t = nullptr;
+    void *d_nms_colrows = nullptr, *d_nms_colwords = nullptr, *d_nms_colcount = nullptr;
     float *h_rec = nullptr;
     void *h_small = nullptr;
     void *h_export = nullptr;  // counts + first records of the frame (export_results)

@@ -201,46 +201,57 @@ struct DecodeArgs {
     float aw, al, ah, az, ayaw0, ayaw1;
     const int32_t *head_counts;  // [ceil(H2 W2 / 16)] from head1x1 with the same thr; 16-byte aligned
     float *rec;            // [n_anchors][9]: box 7, score, index bits
+    uint32_t *key;         // [n_anchors] or NULL: nms_key of every record's score
     int32_t *count;        // total kept
 };
 constexpr int kDecodeTile = 1024;
 hipError_t decode(const DecodeArgs &a, hipStream_t s);
-// The frame's result into pinned host memory: words 0 and 1 of `host` the
-// counts *count0 and *count1 (0 without count1), and from byte 64 the first
-// min(*count1 or *count0, first) 36-byte records of `recs`; written with
-// vector stores and fenced at system scope; then 1 is stored to word 2 with
-// release semantics at system scope, so a host that cleared word 2 before
-// enqueuing the kernel and then reads 1 there (acquire) also sees the counts
-// and records, without waiting for the stream.
-hipError_t export_results(const int32_t *count0, const int32_t *count1, const float *recs, int first, void *host,
-                          hipStream_t s);
+// The result of a frame without NMS into pinned host memory: word 0 of `host`
+// the count (word 1: 0; with NMS, word 0 the decoded and word 1 the kept
+// count), and from byte 64 the first min(*count, first) 36-byte records of
+// `recs`; written with vector stores and fenced at system scope; then 1 is
+// stored to word 2 with release semantics at system scope, so a host that
+// cleared word 2 before enqueuing the kernel and then reads 1 there (acquire)
+// also sees the counts and records, without waiting for the stream.
+hipError_t export_results(const int32_t *count, const float *recs, int first, void *host, hipStream_t s);
 
 // Rotated NMS of the decoded records (see nms.hip).
 constexpr int kNmsMaxCandidates = 16384;
-constexpr int kNmsFootDoubles = 8;
-constexpr int kNmsRankSplits = 16;  // per candidate: x, y, w, l, cos yaw, sin yaw, valid, pad
+constexpr int kNmsFootDoubles = 8;  // per candidate: x, y, w, l, cos yaw, sin yaw, valid, circumradius
+// Ranking key of a score: its order-preserving image.  Flips the sign bit of
+// a non-negative float and every bit of a negative one, which orders all
+// finite and infinite values like the numbers (-0 is taken as +0); a NaN, and
+// nothing else, maps to 0.
+__device__ inline uint32_t nms_key(float score) {
+    const uint32_t bits = score == 0.f ? 0u : __float_as_uint(score);
+    return score != score ? 0u : (bits >> 31) ? ~bits : (bits | 0x80000000u);
+}
 struct NmsArgs {
     const float *rec;             // [n][9] decoded records, ascending anchor index
     const int32_t *count;         // n, on the device
-    int32_t *rank;                // [max_records]
-    int32_t *flag;                // [max_records]
+    const uint32_t *key;          // [n] nms_key of every score
     int32_t *order;               // [max_candidates]
     double *foot;                 // [max_candidates][kNmsFootDoubles]
-    unsigned long long *mask;     // [max_candidates][max_candidates / 64] (rounded up)
     unsigned long long *mask_t;   // [max_candidates]: earlier rows of its own 64-row chunk that suppress it
-    int32_t *partial;             // [kNmsRankSplits][max_records] partial rank counts
-    int32_t *colrows;             // [64 W (W - 1) / 2], W = words per mask row: listed rows per column chunk
-    int32_t *colcount;            // [W] rows listed per column chunk
+    int32_t *colrows;             // [nms_listed]: rows listed per column chunk
+    unsigned long long *colwords; // [nms_listed]: their words, bit b: the row suppresses candidate b of the chunk
+    int32_t *colcount;            // [ceil(max_candidates / 64)] rows listed per column chunk
     float *out;                   // [max_candidates][9] kept records, ascending anchor index
     int32_t *out_count;           // kept, on the device
     double iou_threshold;         // suppress iff IoU > threshold
     int32_t max_candidates;       // 1 .. kNmsMaxCandidates
     int32_t *bad_score = nullptr; // optional: set to 1 if a score is NaN (the caller clears it)
+    // Optional: the frame's result into pinned host memory, as export_results
+    // writes it (counts n and kept, the first host_first kept records, flag).
+    uint32_t *host = nullptr;
+    int32_t host_first = 0;
 };
+// Keys of n caller-provided records; count[0] = n, count[1] = count[2] = 0.
+hipError_t nms_keys(const float *rec, int32_t n, uint32_t *key, int32_t *count, hipStream_t s);
 // max_records bounds n (the grid of the per-record kernels).
 hipError_t rotated_nms(const NmsArgs &a, int64_t max_records, hipStream_t s);
-// Elements of NmsArgs::colrows for a candidate cap.
-inline size_t nms_colrows(int32_t max_candidates) {
+// Elements of NmsArgs::colrows and colwords for a candidate cap.
+constexpr size_t nms_listed(int32_t max_candidates) {
     const size_t w = size_t(max_candidates + 63) / 64;
     return 64 * w * (w > 0 ? w - 1 : 0) / 2 + 1;
 }

@@ -474,8 +474,10 @@ __global__ __launch_bounds__(256) void k_decode_write(DecodeArgs a) {
         o[4] = a.al * expf(r[5]);
         o[5] = a.ah * expf(r[6]);
         o[6] = (an ? a.ayaw1 : a.ayaw0) + r[7];
-        o[7] = 1.0f / (1.0f + expf(-r[0]));
+        const float score = 1.0f / (1.0f + expf(-r[0]));
+        o[7] = score;
         o[8] = __int_as_float(ai);
+        if (a.key) a.key[pos] = nms_key(score);
         ++pos;
     }
 }
@@ -518,11 +520,9 @@ hipError_t decode(const DecodeArgs &a, hipStream_t s) {
     return hipGetLastError();
 }
 
-// One block: the counts, then the records as 4-byte words.
-__global__ __launch_bounds__(256) void k_export(const int32_t *count0, const int32_t *count1, const uint32_t *recs,
-                                                int first, uint32_t *host) {
-    const int32_t c0 = *count0, c1 = count1 ? *count1 : 0;
-    const int32_t n = count1 ? c1 : c0;
+// One block: the count, then the records as 4-byte words.
+__global__ __launch_bounds__(256) void k_export(const int32_t *count, const uint32_t *recs, int first, uint32_t *host) {
+    const int32_t n = *count;
     const int words = (n < 0 ? 0 : n < first ? n : first) * 9;
     // 16-byte stores across the bus (host + 64 and recs are 16-byte aligned),
     // then the last words
@@ -531,18 +531,16 @@ __global__ __launch_bounds__(256) void k_export(const int32_t *count0, const int
         reinterpret_cast<uint4 *>(host + 16)[i] = reinterpret_cast<const uint4 *>(recs)[i];
     for (int i = 4 * quads + int(threadIdx.x); i < words; i += 256) host[16 + i] = recs[i];
     if (threadIdx.x == 0) {
-        host[0] = uint32_t(c0);
-        host[1] = uint32_t(c1);
+        host[0] = uint32_t(n);
+        host[1] = 0u;
     }
     __threadfence_system();
     __syncthreads();  // every thread's stores are fenced before the flag
     if (threadIdx.x == 0) __hip_atomic_store(&host[2], 1u, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
 }
 
-hipError_t export_results(const int32_t *count0, const int32_t *count1, const float *recs, int first, void *host,
-                          hipStream_t s) {
-    k_export<<<1, 256, 0, s>>>(count0, count1, reinterpret_cast<const uint32_t *>(recs), first,
-                               static_cast<uint32_t *>(host));
+hipError_t export_results(const int32_t *count, const float *recs, int first, void *host, hipStream_t s) {
+    k_export<<<1, 256, 0, s>>>(count, reinterpret_cast<const uint32_t *>(recs), first, static_cast<uint32_t *>(host));
     return hipGetLastError();
 }
 

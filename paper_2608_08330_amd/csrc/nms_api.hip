@@ -14,11 +14,21 @@ void set_thread_error(const std::string &msg);
 
 namespace {
 
+// The call's device memory, one allocation for every part.
 struct Scratch {
-    void *p[10] = {};
+    void *base = nullptr;
+    size_t bytes = 0;
+    size_t part(size_t b) {
+        const size_t at = bytes;
+        bytes += (b + 255) & ~size_t(255);
+        return at;
+    }
+    template <class T>
+    T *at(size_t off) const {
+        return reinterpret_cast<T *>(static_cast<char *>(base) + off);
+    }
     ~Scratch() {
-        for (void *q : p)
-            if (q) (void)hipFree(q);
+        if (base) (void)hipFree(base);
     }
 };
 
@@ -45,41 +55,34 @@ extern "C" RTCC_API rtcc_status rtcc_rotated_nms(const float *device_records, in
     if (n == 0) return RTCC_OK;
     if (!device_records || !device_out) return fail(RTCC_E_ARG, "NULL records or output");
 
-    const size_t m = size_t(max_candidates);
-    const size_t words = (m + 63) / 64;
+    const size_t m = size_t(max_candidates), listed = rtcc::kern::nms_listed(max_candidates);
     Scratch sc;
-    const size_t sizes[10] = {size_t(n) * 4, size_t(n) * 4, m * 4, m * rtcc::kern::kNmsFootDoubles * 8, m * words * 8, 64,
-                              m * 8, size_t(rtcc::kern::kNmsRankSplits) * size_t(n) * 4,
-                              rtcc::kern::nms_colrows(max_candidates) * 4, words * 4};
-    for (int i = 0; i < 10; ++i) {
-        hipError_t e = hipMalloc(&sc.p[i], sizes[i]);
-        if (e != hipSuccess) return hip_fail(e, "hipMalloc");
-    }
+    const size_t o_count = sc.part(64), o_key = sc.part(size_t(n) * 4), o_order = sc.part(m * 4);
+    const size_t o_foot = sc.part(m * rtcc::kern::kNmsFootDoubles * 8), o_mask_t = sc.part(m * 8);
+    const size_t o_rows = sc.part(listed * 4), o_words = sc.part(listed * 8), o_colcount = sc.part((m + 63) / 64 * 4);
+    hipError_t e = hipMalloc(&sc.base, sc.bytes);
+    if (e != hipSuccess) return hip_fail(e, "hipMalloc");
     hipStream_t s = nullptr;
-    hipError_t e = hipStreamCreateWithFlags(&s, hipStreamNonBlocking);
+    e = hipStreamCreateWithFlags(&s, hipStreamNonBlocking);
     if (e != hipSuccess) return hip_fail(e, "hipStreamCreateWithFlags");
-    // count[0] = n, count[1] = kept, count[2] = NaN-score flag
-    const int32_t init[3] = {int32_t(n), 0, 0};
-    int32_t *count = static_cast<int32_t *>(sc.p[5]);
+    int32_t *count = sc.at<int32_t>(o_count);  // n, kept, NaN-score flag
     int32_t host_out[2] = {0, 0};
     rtcc::kern::NmsArgs a{};
     a.rec = device_records;
     a.count = count;
-    a.rank = static_cast<int32_t *>(sc.p[0]);
-    a.flag = static_cast<int32_t *>(sc.p[1]);
-    a.order = static_cast<int32_t *>(sc.p[2]);
-    a.foot = static_cast<double *>(sc.p[3]);
-    a.mask = static_cast<unsigned long long *>(sc.p[4]);
-    a.mask_t = static_cast<unsigned long long *>(sc.p[6]);
-    a.partial = static_cast<int32_t *>(sc.p[7]);
-    a.colrows = static_cast<int32_t *>(sc.p[8]);
-    a.colcount = static_cast<int32_t *>(sc.p[9]);
+    a.key = sc.at<uint32_t>(o_key);
+    a.order = sc.at<int32_t>(o_order);
+    a.foot = sc.at<double>(o_foot);
+    a.mask_t = sc.at<unsigned long long>(o_mask_t);
+    a.colrows = sc.at<int32_t>(o_rows);
+    a.colwords = sc.at<unsigned long long>(o_words);
+    a.colcount = sc.at<int32_t>(o_colcount);
     a.out = device_out;
     a.out_count = count + 1;
     a.bad_score = count + 2;
     a.iou_threshold = double(iou_threshold);
     a.max_candidates = max_candidates;
-    e = hipMemcpyAsync(count, init, sizeof(init), hipMemcpyHostToDevice, s);
+    e = rtcc::kern::nms_keys(device_records, int32_t(n), sc.at<uint32_t>(o_key), count, s);
     if (e == hipSuccess) e = rtcc::kern::rotated_nms(a, n, s);
     if (e == hipSuccess) e = hipMemcpyAsync(host_out, count + 1, sizeof(host_out), hipMemcpyDeviceToHost, s);
     if (e == hipSuccess) e = hipStreamSynchronize(s);

@@ -17,7 +17,7 @@ void set_thread_error(const std::string &msg);
 namespace {
 
 using rtcc::kern::kNmsFootDoubles;
-using rtcc::kern::kNmsRankSplits;
+using rtcc::kern::nms_listed;
 
 // Limits of one call: records (the anchors of a 256 x 256 head grid) and
 // NMS candidates.
@@ -29,16 +29,14 @@ constexpr size_t align256(size_t b) { return (b + 255) / 256 * 256; }
 
 // Byte offsets of the parts of the scratch array (worst-case sizes).
 constexpr size_t kOffCount = 0;  // n, kept, NaN-score flag
-constexpr size_t kOffRank = kOffCount + 256;
-constexpr size_t kOffFlag = kOffRank + align256(size_t(kMaxRecords) * 4);
-constexpr size_t kOffPartial = kOffFlag + align256(size_t(kMaxRecords) * 4);
-constexpr size_t kOffOrder = kOffPartial + align256(size_t(kNmsRankSplits) * kMaxRecords * 4);
+constexpr size_t kOffKey = kOffCount + 256;
+constexpr size_t kOffOrder = kOffKey + align256(size_t(kMaxRecords) * 4);
 constexpr size_t kOffFoot = kOffOrder + align256(size_t(kMaxCandidates) * 4);
-constexpr size_t kOffMask = kOffFoot + align256(size_t(kMaxCandidates) * kNmsFootDoubles * 8);
-constexpr size_t kOffMaskT = kOffMask + align256(size_t(kMaxCandidates) * kWords * 8);
+constexpr size_t kOffMaskT = kOffFoot + align256(size_t(kMaxCandidates) * kNmsFootDoubles * 8);
 constexpr size_t kOffColRows = kOffMaskT + align256(size_t(kMaxCandidates) * 8);
-constexpr size_t kOffColCount = kOffColRows + align256((64 * kWords * (kWords - 1) / 2 + 1) * 4);
-constexpr size_t kScratchBytes = kOffColCount + align256(size_t(kWords) * 4);  // 11.9 MB
+constexpr size_t kOffColWords = kOffColRows + align256(nms_listed(kMaxCandidates) * 4);
+constexpr size_t kOffColCount = kOffColWords + align256(nms_listed(kMaxCandidates) * 8);
+constexpr size_t kScratchBytes = kOffColCount + align256(size_t(kWords) * 4);  // 2.4 MB
 
 // The scratch.  In host code this name is a host-side stand-in, not a
 // device address: host code uses only the per-device address returned by
@@ -49,15 +47,6 @@ constexpr int kMaxDevices = 64;
 std::mutex g_mu[kMaxDevices];      // one call at a time per device (they share its scratch)
 void *g_scratch[kMaxDevices] = {}; // device address of `scratch` on each device
 std::mutex g_setup_mu;
-
-// n, kept = 0 and the NaN flag = 0, by a kernel (no host-to-device copy)
-__global__ void k_noalloc_counts(int32_t *c, int32_t n) {
-    if (threadIdx.x == 0) {
-        c[0] = n;
-        c[1] = 0;
-        c[2] = 0;
-    }
-}
 
 rtcc_status fail(rtcc_status s, const std::string &msg) {
     rtcc::set_thread_error(msg);
@@ -115,14 +104,12 @@ extern "C" RTCC_API rtcc_status rtcc_rotated_nms_noalloc(const float *device_rec
     rtcc::kern::NmsArgs a{};
     a.rec = device_records;
     a.count = count;
-    a.rank = reinterpret_cast<int32_t *>(p + kOffRank);
-    a.flag = reinterpret_cast<int32_t *>(p + kOffFlag);
-    a.partial = reinterpret_cast<int32_t *>(p + kOffPartial);
+    a.key = reinterpret_cast<uint32_t *>(p + kOffKey);
     a.order = reinterpret_cast<int32_t *>(p + kOffOrder);
     a.foot = reinterpret_cast<double *>(p + kOffFoot);
-    a.mask = reinterpret_cast<unsigned long long *>(p + kOffMask);
     a.mask_t = reinterpret_cast<unsigned long long *>(p + kOffMaskT);
     a.colrows = reinterpret_cast<int32_t *>(p + kOffColRows);
+    a.colwords = reinterpret_cast<unsigned long long *>(p + kOffColWords);
     a.colcount = reinterpret_cast<int32_t *>(p + kOffColCount);
     a.out = device_out;
     a.out_count = count + 1;
@@ -131,8 +118,7 @@ extern "C" RTCC_API rtcc_status rtcc_rotated_nms_noalloc(const float *device_rec
     a.max_candidates = max_candidates;
 
     int32_t host_out[2] = {0, 0};
-    k_noalloc_counts<<<1, 64, 0, s>>>(count, int32_t(n));
-    e = hipGetLastError();
+    e = rtcc::kern::nms_keys(device_records, int32_t(n), reinterpret_cast<uint32_t *>(p + kOffKey), count, s);
     if (e == hipSuccess) e = rtcc::kern::rotated_nms(a, n, s);
     if (e == hipSuccess) e = hipMemcpyAsync(host_out, count + 1, sizeof(host_out), hipMemcpyDeviceToHost, s);
     // the scratch is free for the next call only once this stream is done

@@ -78,6 +78,32 @@ def test_random_scenes(seed, n, spread, clusters, cap, thr):
     assert 0 < kept <= min(n, cap)
 
 
+@pytest.mark.parametrize("n,cap", [(63, 64), (64, 64), (65, 128), (511, 512), (513, 512), (1025, 1000), (131073, 200)])
+def test_counts_at_the_edges_of_tiles(n, cap):
+    """Record counts around the tiles of the ranking (64 records, eighths of
+    the keys), of the suppression matrix (64 x 64) and of the compaction (131,072
+    records per pass), scores of few values so that ties cross the tiles."""
+    rng = np.random.default_rng(n)
+    boxes, scores, anchors = _scene(rng, n, 20.0 if n < 2000 else 400.0, max(1, min(n, 4000) // 6))
+    scores = np.round(scores * 16).astype(np.float32) / 16
+    _check(boxes, scores, anchors, cap, 0.15, "edge %d" % n)
+
+
+def test_longest_chain():
+    """Boxes in a row, each overlapping only its neighbours, ranked along the
+    row: every second one is kept, and each decision needs the one before it
+    (the selection's rounds at their longest)."""
+    n = 1500
+    boxes = np.zeros((n, 7), dtype=np.float32)
+    boxes[:, 0] = 3.0 * np.arange(n)
+    boxes[:, 3], boxes[:, 4], boxes[:, 5] = 1.6, 4.0, 1.5
+    for order in (np.arange(n), np.random.default_rng(2).permutation(n)):
+        scores = np.empty(n, np.float32)
+        scores[order] = np.linspace(1.0, 0.3, n, dtype=np.float32)
+        kept = _check(boxes, scores, np.arange(n, dtype=np.int32), 4096, 0.1, "chain")
+        assert kept == (n + 1) // 2 or order[1] != 1
+
+
 def test_ties_identical_and_invalid_boxes():
     rng = np.random.default_rng(9)
     boxes, scores, anchors = _scene(rng, 300, 10.0, 5)

@@ -58,8 +58,9 @@ class HipExecutor : public Executor {
         // shared between agents.
         const size_t n_max = size_t(p.n_max);
         const size_t n_cells = size_t(p.H) * p.W;
-        const size_t n_tiles = (n_cells + kern::kScanTile - 1) / kern::kScanTile;
-        const size_t over_cap = n_max / size_t(p.d.max_points_per_pillar + 1) + 1;
+        tile_cells_ = kern::pillar_tile_cells(int(n_cells));
+        const size_t n_tiles = (n_cells + tile_cells_ - 1) / tile_cells_;
+        const size_t crowds = n_max / size_t(kern::pfn_crowd(p.d.max_points_per_pillar) + 1) + 1;
         tiles_ = int(n_tiles);
         // Kernel variant and split-K of every conv layer.
         HIP_TRY(hipDeviceGetAttribute(&n_cu_, hipDeviceAttributeMultiprocessorCount, dev_));
@@ -87,7 +88,7 @@ class HipExecutor : public Executor {
             HIP_TRY(alloc(&b.d_pcells, n_max * 4));
             HIP_TRY(alloc(&b.d_pcounts, n_max * 4));
             HIP_TRY(alloc(&b.d_poffs, n_max * 4));
-            HIP_TRY(alloc(&b.d_overfull, over_cap * 4));
+            HIP_TRY(alloc(&b.d_crowded, crowds * 4));
             HIP_TRY(alloc(&b.d_ttotal, n_tiles * 4));
             HIP_TRY(hipMemset(b.d_ttotal, 0, n_tiles * 4));  // the pillar kernels leave it zero
             HIP_TRY(alloc(&b.d_tstart, (n_tiles + 1) * 4));
@@ -95,9 +96,6 @@ class HipExecutor : public Executor {
             HIP_TRY(alloc(&b.d_binned, n_max * 4));
             HIP_TRY(alloc(&b.d_cellb, n_max * 4));
             HIP_TRY(alloc(&b.d_rank, n_max * 4));
-            HIP_TRY(alloc(&b.d_tcell, n_cells * 4));
-            HIP_TRY(alloc(&b.d_tcount, n_cells * 4));
-            HIP_TRY(alloc(&b.d_toff, n_cells * 4));
             HIP_TRY(alloc(&b.d_meta, 64));
             HIP_TRY(hipMemset(b.d_meta, 0, 64));  // no pillars of a previous frame
             HIP_TRY(alloc(&b.d_canvas, n_cells * p.c_pfn * p.elt));
@@ -135,15 +133,12 @@ class HipExecutor : public Executor {
             pb[k].binned = static_cast<int32_t *>(b.d_binned);
             pb[k].cellb = static_cast<int32_t *>(b.d_cellb);
             pb[k].rank = static_cast<int32_t *>(b.d_rank);
-            pb[k].tcell = static_cast<int32_t *>(b.d_tcell);
-            pb[k].tcount = static_cast<int32_t *>(b.d_tcount);
-            pb[k].toff = static_cast<int32_t *>(b.d_toff);
             pb[k].npil = static_cast<int32_t *>(b.d_npil);
             pb[k].meta = static_cast<int32_t *>(b.d_meta);
             pb[k].pcells = static_cast<int32_t *>(b.d_pcells);
             pb[k].pcounts = static_cast<int32_t *>(b.d_pcounts);
             pb[k].poffs = static_cast<int32_t *>(b.d_poffs);
-            pb[k].overfull = static_cast<int32_t *>(b.d_overfull);
+            pb[k].crowded = static_cast<int32_t *>(b.d_crowded);
             pb[k].member = static_cast<int32_t *>(b.d_member);
             pb[k].sorted = static_cast<float4 *>(b.d_sorted);
             pb[k].canvas = b.d_canvas;
@@ -698,10 +693,9 @@ class HipExecutor : public Executor {
         float *staging = nullptr;
         void *d_pts = nullptr, *d_cell = nullptr, *d_slot = nullptr, *d_member = nullptr;
         void *d_sorted = nullptr;  // points in segment (pillar) order
-        void *d_pcells = nullptr, *d_pcounts = nullptr, *d_poffs = nullptr, *d_overfull = nullptr;
+        void *d_pcells = nullptr, *d_pcounts = nullptr, *d_poffs = nullptr, *d_crowded = nullptr;
         void *d_ttotal = nullptr, *d_tstart = nullptr, *d_npil = nullptr, *d_meta = nullptr;
         void *d_binned = nullptr, *d_cellb = nullptr, *d_rank = nullptr;
-        void *d_tcell = nullptr, *d_tcount = nullptr, *d_toff = nullptr;  // the tiles' pillar lists
         void *d_canvas = nullptr, *d_slotbuf = nullptr, *d_ws = nullptr;
         void *d_warped = nullptr;        // ego-frame map (warp in the branch)
         const void *ego_map = nullptr;   // what the fusion reads when the warp is in the branch
@@ -778,9 +772,9 @@ class HipExecutor : public Executor {
     // every launch): cell ids, scans, scatter, PFN canvas.  With timing, each
     // member's node times for them are those of the first member's ev[1] /
     // ev[2] / ev[3].
-    // With clear_ev, the launches after the first wait for it (the frame's
-    // canvas clear reads the members' last pillar lists, which bin_scatter
-    // and pillar_lists rewrite; bin_count runs beside it).
+    // With clear_ev, the launches that rewrite the members' last pillar lists,
+    // which the frame's canvas clear reads, wait for it (bin_count runs beside
+    // it).
     rtcc_status enqueue_pillars(const int *agents, int m, hipStream_t s, bool timing, hipEvent_t clear_ev,
                                 std::string &err) {
         const Plan &p = p_;
@@ -791,6 +785,7 @@ class HipExecutor : public Executor {
         grp.n_max = 0;
         grp.n_cells = n_cells;
         grp.tiles = tiles_;
+        grp.tile_cells = tile_cells_;
         for (int j = 0; j < m; ++j) {
             const Branch &b = br_[agents[j]];
             grp.agent[j] = agents[j];
@@ -807,11 +802,15 @@ class HipExecutor : public Executor {
         // Between frames the canvas is zero outside the last frame's pillars
         // (prepare_branch).
         for (int j = 0; j < m; ++j) br_[agents[j]].pillars_clean = false;
-        HIP_TRY(kern::bin_count(grp, g, s));
-        if (clear_ev) HIP_TRY(hipStreamWaitEvent(s, clear_ev, 0));
-        HIP_TRY(kern::bin_scatter(grp, s));
-        HIP_TRY(kern::tile_sort(grp, p.d.max_points_per_pillar, s));
-        HIP_TRY(kern::pillar_lists(grp, s));
+        if (kern::pillars_small_fits(n_cells, grp.n_max)) {
+            if (clear_ev) HIP_TRY(hipStreamWaitEvent(s, clear_ev, 0));
+            HIP_TRY(kern::pillars_small(grp, g, kern::pfn_crowd(p.d.max_points_per_pillar), s));
+        } else {
+            HIP_TRY(kern::bin_count(grp, g, s));
+            if (clear_ev) HIP_TRY(hipStreamWaitEvent(s, clear_ev, 0));
+            HIP_TRY(kern::bin_scatter(grp, s));
+            HIP_TRY(kern::tile_sort(grp, kern::pfn_crowd(p.d.max_points_per_pillar), s));
+        }
         HIP_TRY(mark(2));
 
         HIP_TRY(kern::pfn_canvas(p.bf16, pfn_args(), grp, grp.n_max < n_cells ? grp.n_max : n_cells, s));
@@ -1151,6 +1150,7 @@ class HipExecutor : public Executor {
         grp.n_max = b.n;
         grp.n_cells = n_cells;
         grp.tiles = tiles_;
+        grp.tile_cells = tile_cells_;
         kern::PfnArgs pa = pfn_args();
         pa.replay = 1;
         pa.canvas = d_canvas_view_;
@@ -1167,6 +1167,7 @@ class HipExecutor : public Executor {
         pa.b = static_cast<const float *>(d_bias) + p.pfn_b_off;
         pa.C = p.c_pfn;
         pa.max_pts = p.d.max_points_per_pillar;
+        pa.crowd = kern::pfn_crowd(pa.max_pts);
         pa.inv_hx = float(2.0 / (double(p.d.x_max) - double(p.d.x_min)));
         pa.inv_hy = float(2.0 / (double(p.d.y_max) - double(p.d.y_min)));
         pa.z0 = p.d.z_min;
@@ -1361,7 +1362,7 @@ class HipExecutor : public Executor {
     bool idle_ = true;                   // no work queued since the last completed join
     static constexpr size_t kFirstRecords = 1024;  // records read back with the counts
     void *d_pbufs_ = nullptr;            // kern::PillarBufs of every agent
-    int tiles_ = 0;                      // tiles of cells of the pillar sort
+    int tiles_ = 0, tile_cells_ = 0;     // tiles of cells of the pillar sort
     int64_t graph_stats_[3] = {0, 0, 0}; // instantiations, update attempts, launches
 };
 

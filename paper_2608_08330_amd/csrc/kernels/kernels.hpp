@@ -18,20 +18,26 @@ struct PillarGeom {
     int H, W;
 };
 
-constexpr int kScanTile = 2048;  // cells per block of the cell scans
+// Cells per tile of the pillar sort (PillarGroup::tile_cells): fine tiles up to
+// kFineCells cells, for enough blocks on small grids (352 x 100 cells: 69
+// blocks instead of 18 per agent); above, coarse ones, as every 512-point
+// block reserves a run in each tile it touches (at 512 x 512 cells fine tiles
+// would take an atomic per point).
+constexpr int kTileCells = 2048, kTileCellsFine = 512, kFineCells = 131072;
+inline int pillar_tile_cells(int n_cells) { return n_cells <= kFineCells ? kTileCellsFine : kTileCells; }
 
 hipError_t fill_i32(int32_t *p, int64_t n, int32_t v, hipStream_t s);
 
 // One agent's pillar-stage buffers (device pointers, fixed for a context).
-// With tiles = ceil(H*W / kScanTile) tiles of cells, the sizes are: cell,
+// With tiles = ceil(H*W / tile_cells) tiles of cells, the sizes are: cell,
 // slot, binned, cellb, rank, member [n_max]; sorted [n_max] points; ttotal
-// [tiles] (zero between frames); tstart [tiles + 1]; npil [tiles]; tcell, tcount, toff
-// [H*W]; pcells, pcounts, poffs [min(n_max, H*W)]; overfull
-// [n_max / (max_pts + 1) + 1]; meta [3]; canvas [H*W][C].
+// [tiles] (zero between frames); tstart [tiles + 1]; npil [tiles]; pcells,
+// pcounts, poffs [min(n_max, H*W)]; crowded [n_max / (pfn_crowd(max_pts) + 1)
+// + 1]; meta [4] (valid points, pillars, crowded pillars, tiles taken); canvas
+// [H*W][C].
 struct PillarBufs {
-    int32_t *cell, *slot, *ttotal, *tstart, *binned, *cellb, *rank;
-    int32_t *tcell, *tcount, *toff, *npil;
-    int32_t *pcells, *pcounts, *poffs, *overfull, *member, *meta;
+    int32_t *cell, *slot, *ttotal, *tstart, *binned, *cellb, *rank, *npil;
+    int32_t *pcells, *pcounts, *poffs, *crowded, *member, *meta;
     float4 *sorted;
     void *canvas;
 };
@@ -50,8 +56,12 @@ struct PillarGroup {
     int32_t m;       // agents in the group, 1..kMaxGroup
     int32_t n_max;   // max over the group of n[j]
     int32_t n_cells; // H * W
-    int32_t tiles;   // ceil(n_cells / kScanTile)
+    int32_t tiles;   // ceil(n_cells / tile_cells)
+    int32_t tile_cells; // kTileCells or kTileCellsFine
 };
+
+// Points from which on a pillar is crowded: above the cap, and above a few.
+inline int32_t pfn_crowd(int32_t max_pts) { return max_pts < 4 ? max_pts : 4; }
 
 // The sort of points by cell (counting in LDS):
 // K1 bin_count: cell id per point (-1 if dropped); per block of
@@ -60,21 +70,23 @@ struct PillarGroup {
 //    zero) reserving the block's run in the tile, and each point's
 //    position within its tile (slot).
 // K2 bin_scatter: tstart[t] = first point of tile t in tile order,
-//    tstart[tiles] = meta[0] = valid points, meta[2] (overfull count) = 0;
-//    binned / cellb = point index / cell in tile order.
+//    tstart[tiles] = meta[0] = valid points, meta[2] (crowded count), meta[3]
+//    and npil = 0; binned / cellb = point index / cell in tile order.
 // K3 tile_sort: per tile, LDS counts of its cells: the tile's pillars in
-//    ascending cell order at tcell / tcount / toff [tile * kScanTile + q]
-//    (npil[tile] of them), the pillars over max_pts listed in overfull
-//    (by that index, meta[2] of them), and member / sorted = the points in
-//    cell order (rank within a cell: an arbitrary order).
+//    ascending cell order at their place in the global lists pcells / pcounts
+//    / poffs (npil[tile] - 1 of them), the pillars of more than `crowd` points
+//    listed in crowded (by that place, meta[2] of them), member / sorted = the points in
+//    cell order (rank within a cell: an arbitrary order); meta[1] = P pillars;
+//    ttotal back to zero.
 hipError_t bin_count(const PillarGroup &grp, const PillarGeom &g, hipStream_t s);
 hipError_t bin_scatter(const PillarGroup &grp, hipStream_t s);
-hipError_t tile_sort(const PillarGroup &grp, int32_t max_pts, hipStream_t s);
-// K4 pillar_lists: the global pillar lists pcells / pcounts / poffs in
-// ascending cell order, meta[1] = P pillars, from the tiles' lists;
-// ttotal back to zero.
-hipError_t pillar_lists(const PillarGroup &grp, hipStream_t s);
-// K5 pfn_canvas: the dense canvas [H*W][C]: per pillar cell, channel max over the first
+hipError_t tile_sort(const PillarGroup &grp, int32_t crowd, hipStream_t s);
+// K1 to K3 in one launch, one block per agent, for small inputs: the same
+// lists, member and sorted points.
+constexpr int kSmallPoints = 16384, kSmallCells = 65536;
+inline bool pillars_small_fits(int n_cells, int n_max) { return n_cells <= kSmallCells && n_max <= kSmallPoints; }
+hipError_t pillars_small(const PillarGroup &grp, const PillarGeom &g, int32_t crowd, hipStream_t s);
+// K4 pfn_canvas: the dense canvas [H*W][C]: per pillar cell, channel max over the first
 // min(count, max_pts) members of ReLU(W^T f + b) (for cells over the cap,
 // after moving the max_pts lowest point indices to the front of the
 // segment).  Writes the pillar cells only: every other cell must already be
@@ -84,8 +96,9 @@ struct PfnArgs {
     const float *b;  // [C]
     int32_t C;
     int32_t max_pts;
+    int32_t crowd;  // pfn_crowd(max_pts): pillars of more points take a wavefront each
     float inv_hx, inv_hy, z0, inv_dz;
-    int32_t pillar_blocks;  // set by pfn_canvas
+    int32_t crowd_blocks;  // set by pfn_canvas
     // replay = 1: the pillars over the cap already hold their selected points
     // first (a previous launch on the same lists chose them), so they are
     // not chosen again; the canvas cells come out bit for bit as in that

@@ -1,30 +1,34 @@
 // Pillarization and point-feature canvas for gfx950.
 //
-// Deterministic sort of points by cell (LDS, one global atomic per non-empty (point block, tile) bin, no
-// order-dependent result), five dependent launches, each
-// over a group of agents released together (the blocks of the group's
-// agents are interleaved, see group_block; a single release is a group of
-// one).  Cells are cut into tiles of kScanTile cells, points into blocks of
-// kPtsPerBlock:
+// Deterministic sort of points by cell (LDS, no order-dependent result), over
+// a group of agents released together (the blocks of the group's agents are
+// interleaved, see group_block; a single release is a group of one).
+// Small inputs (pillars_small_fits) take one launch before the point-feature
+// net, one block per agent:
+//   pillars_small LDS counts of every cell (16 bits each), each point's rank in
+//                its cell from the LDS atomic, a block scan over the cells ->
+//                the pillar lists and each point's place in cell order
+// Larger ones three.  Cells are cut into tiles of PillarGroup::tile_cells,
+// points into blocks of kPtsPerBlock:
 //   bin_count    cell id per point; per point block, an LDS histogram of its
 //                points over the tiles, the point's rank in its (block,
 //                tile) bin from the LDS atomic; every non-empty bin
-//                reserves its run in its tile (the only global atomics: one
-//                per non-empty bin, not one per point)
+//                reserves its run in its tile (one global atomic per
+//                non-empty bin, not one per point)
 //   bin_scatter  the tiles' first points (each block scans the tiles'
 //                totals itself), point indices and cells in tile order
 //   tile_sort    one block per tile: LDS counts of the tile's cells, their
 //                scan -> the tile's pillars in ascending cell order and
-//                each point's place in cell order (member, sorted)
-//   pillar_lists one block per tile: its pillar list moved to its place in
-//                the global lists (the block adds up the earlier tiles'
-//                pillar counts itself)
+//                each point's place in cell order (member, sorted); the
+//                block publishes its pillar count, adds up those of the
+//                tiles before it and writes its part of the global lists
+// Then for both:
 //   pfn_canvas   one lane per (two pillars, 8 channels): linear 4 -> C,
 //                ReLU, max over the pillar's points into its cell.  Extra
-//                blocks take the few pillars over the cap: one wavefront
-//                moves the cap lowest point indices (found by bisection on
-//                the index value) to the front of the segment and writes
-//                that pillar's features
+//                blocks take the crowded pillars, one wavefront each, and
+//                move the cap lowest point indices (found by bisection on
+//                the index value) of those over the cap to the front of the
+//                segment
 // The canvas is zero outside the pillars: canvas_clear zeroes the last
 // frame's pillar cells again (off the encoder's path: the executor runs it
 // when the next frame begins, before any branch input has arrived).
@@ -32,6 +36,7 @@
 // segment, and every consumer of it is order-independent (max, set
 // selection), so every output is bitwise reproducible.
 #include <climits>
+#include <type_traits>
 
 #include "kernels.hpp"
 
@@ -39,6 +44,8 @@ namespace rtcc {
 namespace kern {
 
 namespace {
+
+typedef float f32x4_t __attribute__((ext_vector_type(4)));
 
 __device__ inline int2 add2(int2 a, int2 b) { return make_int2(a.x + b.x, a.y + b.y); }
 
@@ -138,7 +145,7 @@ __global__ __launch_bounds__(256) void k_bin_count(const PillarGroup grp, const 
             const int c = cell_of(pts[i], g);
             B.cell[i] = c;
             if (c >= 0) {
-                tile[u] = c / kScanTile;
+                tile[u] = c / grp.tile_cells;
                 rank[u] = atomicAdd(&hist[tile[u]], 1);
             }
         }
@@ -184,11 +191,15 @@ __global__ __launch_bounds__(256) void k_bin_scatter(const PillarGroup grp) {
     if (threadIdx.x == 0) ts[T] = tot.x;
     __syncthreads();
     if (gb.b == 0) {
-        for (int t = threadIdx.x; t <= T; t += 256) B.tstart[t] = ts[t];
+        for (int t = threadIdx.x; t <= T; t += 256) {
+            B.tstart[t] = ts[t];
+            if (t < T) B.npil[t] = 0;  // not published yet
+        }
         if (threadIdx.x == 0) {
             B.meta[0] = tot.x;
-            B.meta[1] = 0;  // the pillar lists' kernel writes the pillar count
-            B.meta[2] = 0;  // pillars over the cap, appended to by the tile sort
+            B.meta[1] = 0;  // the last tile writes the pillar count
+            B.meta[2] = 0;  // crowded pillars, appended to by the tile sort
+            B.meta[3] = 0;  // tiles taken
         }
     }
     if (gb.b >= blocks_of(n)) return;
@@ -198,7 +209,7 @@ __global__ __launch_bounds__(256) void k_bin_scatter(const PillarGroup grp) {
         if (i < n) {
             const int c = B.cell[i];
             if (c >= 0) {
-                const int d = ts[c / kScanTile] + B.slot[i];
+                const int d = ts[c / grp.tile_cells] + B.slot[i];
                 B.binned[d] = i;
                 B.cellb[d] = c;
             }
@@ -206,19 +217,26 @@ __global__ __launch_bounds__(256) void k_bin_scatter(const PillarGroup grp) {
     }
 }
 
-// K4: one block per tile of cells.
+// K3: one block per tile of cells; 256 threads, CPT cells each.  A block takes
+// its tile by a ticket, so the blocks of all earlier tiles have started when
+// it waits for their pillar counts (each is published before its block waits
+// for anything): the wait always ends.
 constexpr int kSortCache = 8;
-__global__ __launch_bounds__(256) void k_tile_sort(const PillarGroup grp, int32_t max_pts) {
-    __shared__ int cnt[kScanTile];
-    __shared__ int loff[kScanTile];
-    const GroupBlock gb = group_block(grp);
-    const int j = gb.j, t = gb.b;
+template <int CPT>
+__global__ __launch_bounds__(256) void k_tile_sort(const PillarGroup grp, int32_t crowd) {
+    constexpr int CELLS = 256 * CPT;
+    __shared__ int cnt[CELLS];
+    __shared__ int loff[CELLS];
+    __shared__ int ticket, first_crowded;
+    const int j = group_block(grp).j;
     const PillarBufs B = group_bufs(grp, j);
     const float4 *pts = grp.pts[j];
-    const int lo = B.tstart[t], hi = B.tstart[t + 1];
-    const int c0 = t * kScanTile;
-    for (int q = threadIdx.x; q < kScanTile; q += 256) cnt[q] = 0;
+    if (threadIdx.x == 0) ticket = atomicAdd(&B.meta[3], 1);
+    for (int q = threadIdx.x; q < CELLS; q += 256) cnt[q] = 0;
     __syncthreads();
+    const int t = ticket;
+    const int lo = B.tstart[t], hi = B.tstart[t + 1];
+    const int c0 = t * CELLS;
     // the tile's first kSortCache * 256 points keep their cell and rank in
     // registers between the passes; any further ones go through `rank`
     int lcell[kSortCache], rk[kSortCache];
@@ -233,32 +251,26 @@ __global__ __launch_bounds__(256) void k_tile_sort(const PillarGroup grp, int32_
     for (int e = lo + int(threadIdx.x) + kSortCache * 256; e < hi; e += 256)
         B.rank[e] = atomicAdd(&cnt[B.cellb[e] - c0], 1);
     __syncthreads();
-    int v[8];
-    int s = 0, f = 0;
+    int v[CPT];
+    int s = 0, f = 0;  // points; pillars, and the crowded ones above 16 bits
 #pragma unroll
-    for (int i = 0; i < 8; ++i) {
-        v[i] = cnt[threadIdx.x * 8 + i];
+    for (int i = 0; i < CPT; ++i) {
+        v[i] = cnt[threadIdx.x * CPT + i];
         s += v[i];
-        f += v[i] > 0;
+        f += int(v[i] > 0) + (int(v[i] > crowd) << 16);
     }
     int2 tot;
     const int2 ex = block_excl_scan256(make_int2(s, f), &tot);
-    int off = ex.x, q = ex.y;
+    if (threadIdx.x == 0) {
+        __hip_atomic_store(&B.npil[t], (tot.y & 0xffff) + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        first_crowded = tot.y >> 16 ? atomicAdd(&B.meta[2], tot.y >> 16) : 0;
+    }
+    int off = ex.x;
 #pragma unroll
-    for (int i = 0; i < 8; ++i) {
-        const int lc = int(threadIdx.x) * 8 + i;
-        loff[lc] = off;
-        if (v[i] > 0) {
-            const int sidx = c0 + q;
-            B.tcell[sidx] = c0 + lc;
-            B.tcount[sidx] = v[i];
-            B.toff[sidx] = lo + off;
-            if (v[i] > max_pts) B.overfull[atomicAdd(&B.meta[2], 1)] = sidx;
-            ++q;
-        }
+    for (int i = 0; i < CPT; ++i) {
+        loff[threadIdx.x * CPT + i] = off;
         off += v[i];
     }
-    if (threadIdx.x == 0) B.npil[t] = tot.y;
     __syncthreads();
     int idx[kSortCache];
 #pragma unroll
@@ -281,30 +293,147 @@ __global__ __launch_bounds__(256) void k_tile_sort(const PillarGroup grp, int32_
         B.member[d] = i;
         B.sorted[d] = pts[i];
     }
+    // the tile's pillars to their place in the global lists, behind those of
+    // the tiles before it
+    int before = 0;
+    for (int q = threadIdx.x; q < t; q += 256) {
+        int np;
+        while ((np = __hip_atomic_load(&B.npil[q], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) == 0) __builtin_amdgcn_s_sleep(1);
+        before += np - 1;
+    }
+    int2 all;
+    block_excl_scan256(make_int2(before, 0), &all);
+    int p = all.x + (ex.y & 0xffff), k = first_crowded + (ex.y >> 16);
+    off = ex.x;
+#pragma unroll
+    for (int i = 0; i < CPT; ++i) {
+        if (v[i] > 0) {
+            B.pcells[p] = c0 + int(threadIdx.x) * CPT + i;
+            B.pcounts[p] = v[i];
+            B.poffs[p] = lo + off;
+            if (v[i] > crowd) B.crowded[k++] = p;
+            ++p;
+        }
+        off += v[i];
+    }
+    if (threadIdx.x == 0) {
+        if (t == grp.tiles - 1) B.meta[1] = all.x + (tot.y & 0xffff);
+        // the tile's point total back to zero, the state the next frame's
+        // bin count starts from (every reader of it has finished)
+        B.ttotal[t] = 0;
+    }
 }
 
-// K5: the tiles' pillar lists concatenated into the global ones, one block
-// per tile: its first global pillar is the sum of the earlier tiles'
-// pillar counts.  The last tile's block writes the pillar count.
-__global__ __launch_bounds__(256) void k_pillar_lists(const PillarGroup grp) {
-    const GroupBlock gb = group_block(grp);
-    const int t = gb.b;
-    const PillarBufs B = group_bufs(grp, gb.j);
-    int s = 0;
-    for (int q = threadIdx.x; q < t; q += 256) s += B.npil[q];
-    int2 tot;
-    block_excl_scan256(make_int2(s, 0), &tot);
-    const int first = tot.x, np = B.npil[t];
-    const int c0 = t * kScanTile;
-    for (int q = threadIdx.x; q < np; q += 256) {
-        B.pcells[first + q] = B.tcell[c0 + q];
-        B.pcounts[first + q] = B.tcount[c0 + q];
-        B.poffs[first + q] = B.toff[c0 + q];
+// The whole sort of one agent in one block: at most kSmallPoints points and
+// CELLS cells, two 16-bit counts (then offsets) per LDS word.  Bound by latency
+// and by what one CU can issue (16 wavefronts): the line is where it takes as
+// long as the three launches.  2,000 points on 4,096 cells 20 -> 10.8 us, 6,000
+// on 2,640 38 -> 16.5 (one launch for four); six agents with 4,000 points on
+// 35,200 cells each 19 -> 18.9.
+constexpr int kSmallPerThread = kSmallPoints / 1024;
+static_assert(kSmallPerThread == 16, "four runs of four points per thread");
+template <int CELLS>
+__global__ __launch_bounds__(1024) void k_pillars_small(const PillarGroup grp, const PillarGeom g, int32_t crowd) {
+    __shared__ uint32_t cnt[CELLS / 2];
+    __shared__ int2 wsum[16];
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int j = blockIdx.x;
+    const int n = grp.n[j];
+    const PillarBufs B = group_bufs(grp, j);
+    const f32x4_t *pv = reinterpret_cast<const f32x4_t *>(grp.pts[j]);
+    const int words = (grp.n_cells + 1) / 2;
+    for (int w = tid; w < words; w += 1024) cnt[w] = 0u;
+    __syncthreads();
+    // four points of a thread at a time, their loads in flight together
+    int at[kSmallPerThread];  // cell + (rank in the cell << 16); -1: dropped
+    auto count4 = [&](auto first) {
+        constexpr int u0 = decltype(first)::value;
+#pragma unroll
+        for (int u = 0; u < 4; ++u) at[u0 + u] = -1;
+        if (u0 * 1024 >= n) return;
+        f32x4_t q[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            const int i = (u0 + u) * 1024 + tid;
+            q[u] = i < n ? pv[i] : f32x4_t{INFINITY, 0.f, 0.f, 0.f};  // no cell
+        }
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            const int c = cell_of(make_float4(q[u].x, q[u].y, q[u].z, q[u].w), g);
+            if (c >= 0) {
+                const int sh = (c & 1) * 16;
+                at[u0 + u] = c | int(((atomicAdd(&cnt[c >> 1], 1u << sh) >> sh) & 0xffffu) << 16);
+            }
+        }
+    };
+    count4(std::integral_constant<int, 0>{});
+    count4(std::integral_constant<int, 4>{});
+    count4(std::integral_constant<int, 8>{});
+    count4(std::integral_constant<int, 12>{});
+    __syncthreads();
+    // an odd number of consecutive words per thread: no bank conflicts
+    const int per = ((words + 1023) / 1024) | 1;
+    const int w0 = tid * per < words ? tid * per : words, w1 = w0 + per < words ? w0 + per : words;
+    int2 v = make_int2(0, 0);  // points; pillars, and the crowded ones above 16 bits
+#pragma unroll 4
+    for (int w = w0; w < w1; ++w) {
+        const int a = cnt[w] & 0xffffu, b = cnt[w] >> 16;
+        v.x += a + b;
+        v.y += int(a > 0) + int(b > 0) + ((int(a > crowd) + int(b > crowd)) << 16);
     }
-    if (t == grp.tiles - 1 && threadIdx.x == 0) B.meta[1] = first + np;
-    // the tile's point total back to zero, the state the next frame's bin
-    // count starts from (every reader of it has finished)
-    if (threadIdx.x == 0) B.ttotal[t] = 0;
+    const int2 inc = wave_incl_scan(v);
+    if (lane == 63) wsum[wave] = inc;
+    __syncthreads();
+    int2 base = make_int2(0, 0), tot = make_int2(0, 0);
+#pragma unroll
+    for (int q = 0; q < 16; ++q) {
+        if (q < wave) base = add2(base, wsum[q]);
+        tot = add2(tot, wsum[q]);
+    }
+    const int before = base.y + inc.y - v.y;
+    int off = base.x + inc.x - v.x, p = before & 0xffff, k = before >> 16;
+    for (int w = w0; w < w1; ++w) {
+        const uint32_t both = cnt[w];
+        cnt[w] = uint32_t(off) | (uint32_t(off + int(both & 0xffffu)) << 16);
+        auto list = [&](int c, int count) {
+            if (count == 0) return;
+            B.pcells[p] = c;
+            B.pcounts[p] = count;
+            B.poffs[p] = off;
+            if (count > crowd) B.crowded[k++] = p;
+            off += count;
+            ++p;
+        };
+        list(2 * w, int(both & 0xffffu));
+        list(2 * w + 1, int(both >> 16));
+    }
+    __syncthreads();
+    auto place4 = [&](auto first) {
+        constexpr int u0 = decltype(first)::value;
+        if (u0 * 1024 >= n) return;
+        f32x4_t q[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u)
+            if (at[u0 + u] >= 0) q[u] = pv[(u0 + u) * 1024 + tid];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            if (at[u0 + u] >= 0) {
+                const int c = at[u0 + u] & 0xffff;
+                const int d = int((cnt[c >> 1] >> ((c & 1) * 16)) & 0xffffu) + (at[u0 + u] >> 16);
+                B.member[d] = (u0 + u) * 1024 + tid;
+                reinterpret_cast<f32x4_t *>(B.sorted)[d] = q[u];
+            }
+        }
+    };
+    place4(std::integral_constant<int, 0>{});
+    place4(std::integral_constant<int, 4>{});
+    place4(std::integral_constant<int, 8>{});
+    place4(std::integral_constant<int, 12>{});
+    if (tid == 0) {
+        B.meta[0] = tot.x;
+        B.meta[1] = tot.y & 0xffff;
+        B.meta[2] = tot.y >> 16;
+    }
 }
 
 __device__ inline uint32_t pack_bf16x2(float a, float b) {
@@ -349,14 +478,18 @@ __device__ inline void store_canvas8(const PfnArgs &a, void *canvas, int cell, i
     }
 }
 
-// Blocks [0, a.pillar_blocks): a lane per (two pillars, 8 channels) of the
+// Blocks from a.crowd_blocks on: a lane per (two pillars, 8 channels) of the
 // global pillar list takes ReLU(W^T f + b) maxed over the pillar's points,
-// read in segment order from `sorted`, into the pillar's cell.  Pillars
-// over the cap are left to the other blocks.  Blocks from
-// a.pillar_blocks on: one wavefront per pillar over the cap moves the cap
-// lowest point indices to the front of its segment (member indices and
-// points) and writes the features of those points.  The other cells of the
-// canvas already hold zeros.
+// read in segment order from `sorted`, into the pillar's cell.  Crowded
+// pillars (more than a.crowd points) are left to the blocks before them, one
+// wavefront each: a lane that walked a pillar of 20 or 30 points held up its
+// wavefront, and the kernel, for as many loads and 8 times as many
+// multiply-adds in a row.  Of a pillar over the cap that wavefront first moves
+// the cap lowest point indices to the front of its segment (member indices
+// and points).  The other cells of the canvas already hold zeros.  One agent with 40,000 points 16.6 -> 7.3 us, 6,000
+// on 2,640 cells 13.5 -> 5.1, 100,000 on 512 x 512 cells 12.8 -> 10.8 (eight of
+// these in a launch, where the wavefronts have others to hide behind, 38.6 ->
+// 41.8).
 template <bool BF16>
 __global__ __launch_bounds__(256) void k_pfn_canvas(const PfnArgs a, const PillarGroup grp) {
     // PFN weights and bias, read once per block into LDS (C <= 512)
@@ -367,20 +500,41 @@ __global__ __launch_bounds__(256) void k_pfn_canvas(const PfnArgs a, const Pilla
     const int j = gb.j;
     const PillarBufs B = group_bufs(grp, j);
     void *const canvas = a.canvas ? a.canvas : B.canvas;
-    if (gb.b >= a.pillar_blocks) {
-        // pillars over the cap, one wavefront each
+    if (gb.b < a.crowd_blocks) {
+        // crowded pillars, one wavefront each: 8 channels per lane, and where
+        // the channel groups divide the wavefront its lanes share the points
+        // (a maximum does not depend on the order)
         const int lane = threadIdx.x & 63;
-        const int wave = ((gb.b - a.pillar_blocks) * 256 + int(threadIdx.x)) >> 6;
-        const int n_waves = ((gb.nb - a.pillar_blocks) * 256) >> 6;
-        const int n_over = B.meta[2];
+        const int wave = (gb.b * 256 + int(threadIdx.x)) >> 6;
+        const int n_waves = (a.crowd_blocks * 256) >> 6;
+        const int n_crowded = B.meta[2];
         const float4 *pts = grp.pts[j];
-        for (int w = wave; w < n_over; w += n_waves) {
-            const int sidx = B.overfull[w];  // in the tiles' pillar lists
-            const int c = B.tcell[sidx];
-            const int cnt = B.tcount[sidx];
-            int32_t *seg = B.member + B.toff[sidx];
-            float4 *sseg = B.sorted + B.toff[sidx];
-            if (!a.replay) {
+        const int groups = a.C >> 3;
+        const bool share = groups <= 64 && (64 % groups) == 0;
+        const int pg = share ? lane / groups : 0, npg = share ? 64 / groups : 1;
+        float w0[8], w1[8], w2[8], w3[8], bb[8];
+        auto weights = [&](int ch) {
+#pragma unroll
+            for (int i = 0; i < 8; ++i) {
+                w0[i] = sw[0 * a.C + ch + i];
+                w1[i] = sw[1 * a.C + ch + i];
+                w2[i] = sw[2 * a.C + ch + i];
+                w3[i] = sw[3 * a.C + ch + i];
+                bb[i] = sw[4 * a.C + ch + i];
+            }
+        };
+        if (share) weights((lane % groups) * 8);
+        for (int w = wave; w < n_crowded; w += n_waves) {
+            const int p = B.crowded[w];
+            const int c = B.pcells[p];
+            const int cnt = B.pcounts[p];
+            int32_t *seg = B.member + B.poffs[p];
+            float4 *sseg = B.sorted + B.poffs[p];
+            if (cnt > a.max_pts && !a.replay) {
+                // the first 256 members stay in registers
+                int e[4];
+#pragma unroll
+                for (int u = 0; u < 4; ++u) e[u] = u * 64 + lane < cnt ? seg[u * 64 + lane] : INT_MAX;
                 // Smallest T with #{members < T} >= max_pts.  Members are
                 // distinct point indices in [0, n), so exactly max_pts members
                 // lie below T.
@@ -388,9 +542,10 @@ __global__ __launch_bounds__(256) void k_pfn_canvas(const PfnArgs a, const Pilla
                 while (lo < hi) {
                     const int mid = lo + (hi - lo) / 2;
                     int below = 0;
-                    for (int q = lane; q < cnt; q += 64) below += seg[q] < mid;
 #pragma unroll
-                    for (int d = 32; d >= 1; d >>= 1) below += __shfl_xor(below, d, 64);
+                    for (int u = 0; u < 4; ++u) below += __popcll(__ballot(e[u] < mid));
+                    for (int q0 = 256; q0 < cnt; q0 += 64)
+                        below += __popcll(__ballot(q0 + lane < cnt && seg[q0 + lane] < mid));
                     if (below >= a.max_pts) hi = mid;
                     else lo = mid + 1;
                 }
@@ -399,36 +554,37 @@ __global__ __launch_bounds__(256) void k_pfn_canvas(const PfnArgs a, const Pilla
                 // front: a chunk is read completely before any of it is
                 // overwritten, and writes never pass the chunk being read.
                 int pos = 0;
-                for (int base = 0; base < cnt && pos < a.max_pts; base += 64) {
-                    const int q = base + lane;
-                    const int e = q < cnt ? seg[q] : INT_MAX;
-                    const bool sel = q < cnt && e < T;
-                    const unsigned long long m = __ballot(sel);
-                    const int my = pos + __popcll(m & ((1ull << lane) - 1ull));
-                    if (sel) {
-                        seg[my] = e;
-                        sseg[my] = pts[e];
+                auto move = [&](int m) {
+                    const unsigned long long sel = __ballot(m < T);
+                    if (m < T) {
+                        const int my = pos + __popcll(sel & ((1ull << lane) - 1ull));
+                        seg[my] = m;
+                        sseg[my] = pts[m];
                     }
-                    pos += __popcll(m);
-                }
+                    pos += __popcll(sel);
+                };
+#pragma unroll
+                for (int u = 0; u < 4; ++u) move(e[u]);
+                for (int q0 = 256; q0 < cnt && pos < a.max_pts; q0 += 64)
+                    move(q0 + lane < cnt ? seg[q0 + lane] : INT_MAX);
                 // the wave's own writes above are read back by other lanes
                 __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
                 __builtin_amdgcn_wave_barrier();
                 __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
             }
-            for (int ch = lane * 8; ch < a.C; ch += 64 * 8) {
-                float w0[8], w1[8], w2[8], w3[8], bb[8], mx[8];
+            const int used = cnt < a.max_pts ? cnt : a.max_pts;
+            for (int ch = (share ? lane % groups : lane) * 8; ch < a.C; ch += 64 * 8) {
+                if (!share) weights(ch);
+                float mx[8];
 #pragma unroll
-                for (int i = 0; i < 8; ++i) {
-                    w0[i] = sw[0 * a.C + ch + i];
-                    w1[i] = sw[1 * a.C + ch + i];
-                    w2[i] = sw[2 * a.C + ch + i];
-                    w3[i] = sw[3 * a.C + ch + i];
-                    bb[i] = sw[4 * a.C + ch + i];
-                    mx[i] = 0.f;
-                }
-                for (int t = 0; t < a.max_pts; ++t) pfn_point(a, sseg[t], w0, w1, w2, w3, bb, mx);
-                store_canvas8<BF16>(a, canvas, c, ch, mx);
+                for (int i = 0; i < 8; ++i) mx[i] = 0.f;
+#pragma unroll 2
+                for (int t = pg; t < used; t += npg) pfn_point(a, sseg[t], w0, w1, w2, w3, bb, mx);
+                if (share)
+                    for (int d = groups; d < 64; d <<= 1)
+#pragma unroll
+                        for (int i = 0; i < 8; ++i) mx[i] = fmaxf(mx[i], __shfl_xor(mx[i], d, 64));
+                if (pg == 0) store_canvas8<BF16>(a, canvas, c, ch, mx);
             }
         }
         return;
@@ -436,7 +592,7 @@ __global__ __launch_bounds__(256) void k_pfn_canvas(const PfnArgs a, const Pilla
     // two pillars per lane (8 channels of each): their loads are in flight
     // together
     const int lanes_per_cell = a.C >> 3;
-    const int gid = gb.b * 256 + int(threadIdx.x);
+    const int gid = (gb.b - a.crowd_blocks) * 256 + int(threadIdx.x);
     const int pp = gid / lanes_per_cell;
     const int ch = (gid - pp * lanes_per_cell) * 8;
     const int P = B.meta[1];
@@ -447,9 +603,9 @@ __global__ __launch_bounds__(256) void k_pfn_canvas(const PfnArgs a, const Pilla
     const int cell1 = has1 ? B.pcells[p0 + 1] : 0;
     const int cnt1 = has1 ? B.pcounts[p0 + 1] : 0;
     const int off1 = has1 ? B.poffs[p0 + 1] : off0;
-    // pillars over the cap are left to the blocks above
-    const int n0 = cnt0 <= a.max_pts ? cnt0 : 0;
-    const int n1 = cnt1 <= a.max_pts ? cnt1 : 0;
+    // crowded pillars are left to the blocks above
+    const int n0 = cnt0 <= a.crowd ? cnt0 : 0;
+    const int n1 = cnt1 <= a.crowd ? cnt1 : 0;
     float w0[8], w1[8], w2[8], w3[8], bb[8], m0[8], m1[8];
 #pragma unroll
     for (int i = 0; i < 8; ++i) {
@@ -521,21 +677,27 @@ hipError_t bin_scatter(const PillarGroup &grp, hipStream_t s) {
     return hipGetLastError();
 }
 
-hipError_t tile_sort(const PillarGroup &grp, int32_t max_pts, hipStream_t s) {
-    k_tile_sort<<<unsigned(grp.tiles) * unsigned(grp.m), 256, 0, s>>>(grp, max_pts);
+hipError_t tile_sort(const PillarGroup &grp, int32_t crowd, hipStream_t s) {
+    const unsigned g = unsigned(grp.tiles) * unsigned(grp.m);
+    if (grp.tile_cells == kTileCellsFine) k_tile_sort<kTileCellsFine / 256><<<g, 256, 0, s>>>(grp, crowd);
+    else if (grp.tile_cells == kTileCells) k_tile_sort<kTileCells / 256><<<g, 256, 0, s>>>(grp, crowd);
+    else return hipErrorInvalidValue;
     return hipGetLastError();
 }
 
-hipError_t pillar_lists(const PillarGroup &grp, hipStream_t s) {
-    k_pillar_lists<<<unsigned(grp.tiles) * unsigned(grp.m), 256, 0, s>>>(grp);
+hipError_t pillars_small(const PillarGroup &grp, const PillarGeom &g, int32_t crowd, hipStream_t s) {
+    if (!pillars_small_fits(grp.n_cells, grp.n_max)) return hipErrorInvalidValue;
+    if (grp.n_cells <= kSmallCells / 4) k_pillars_small<kSmallCells / 4><<<unsigned(grp.m), 1024, 0, s>>>(grp, g, crowd);
+    else k_pillars_small<kSmallCells><<<unsigned(grp.m), 1024, 0, s>>>(grp, g, crowd);
     return hipGetLastError();
 }
 
 hipError_t pfn_canvas(bool bf16, PfnArgs a, const PillarGroup &grp, int32_t max_pillars, hipStream_t s) {
-    // pillar blocks, then 64 blocks for the cells over the cap when any
-    // agent's cell can exceed it
-    a.pillar_blocks = int32_t(blocks_for(int64_t((max_pillars + 1) / 2) * (a.C / 8), 256));
-    const unsigned blocks = unsigned(a.pillar_blocks) + (grp.n_max > a.max_pts ? 64u : 0u);
+    // blocks for the crowded pillars (four at a time each), which take the
+    // longest, then the others
+    const unsigned crowds = blocks_for(grp.n_max / (a.crowd + 1), 4);
+    a.crowd_blocks = int32_t(crowds < 256u ? crowds : 256u);
+    const unsigned blocks = unsigned(a.crowd_blocks) + blocks_for(int64_t((max_pillars + 1) / 2) * (a.C / 8), 256);
     if (blocks == 0) return hipSuccess;
     const unsigned grid = blocks * unsigned(grp.m);
     if (bf16) k_pfn_canvas<true><<<grid, 256, 0, s>>>(a, grp);

@@ -64,3 +64,42 @@ def test_fifteen_million_points_on_two_tiles():
         run_frame(ctx, fr)
         _check_pillars(ctx, cfg, big, 0)
         _check_pillars(ctx, cfg, fr["points"][1], 1)
+
+
+# (H, W) cells and points: one block per agent up to 16,384 points and 65,536
+# cells (its smaller form up to 16,384 cells), tiles of 512 cells up to 131,072
+# cells and of 2,048 above
+@pytest.mark.parametrize("grid,n", [
+    ((1, 1), 40), ((3, 5), 0), ((3, 5), 1), ((128, 128), 1024), ((128, 129), 1025), ((127, 129), 16384),
+    ((256, 256), 16384), ((256, 256), 16385), ((256, 257), 1023), ((11, 5958), 5000), ((512, 1), 513),
+    ((256, 512), 20000), ((257, 511), 20000), ((2, 70001), 30000),
+])
+def test_sizes_at_the_edges_of_the_paths(grid, n):
+    cfg = synth.config("c1")
+    H, W = grid
+    cfg.update(K=2, n_points=max(n, 1), pillar=0.5, x_range=(0.0, 0.5 * W), y_range=(0.0, 0.5 * H))
+    rng = np.random.default_rng(H * 1000003 + W * 101 + n)
+    _say("%d x %d cells, %d points" % (H, W, n))
+    clouds = []
+    for k in range(2):
+        p = np.empty((n, 4), np.float32)
+        # two thirds spread (some outside), the rest crowded into a few cells
+        p[:, 0] = rng.uniform(-0.3, 0.5 * W + 0.3, n)
+        p[:, 1] = rng.uniform(-0.3, 0.5 * H + 0.3, n)
+        m = n // 3
+        p[:m, 0] = 0.5 * rng.integers(max(0, W - 3), W, m) + 0.2
+        p[:m, 1] = 0.5 * rng.integers(max(0, H - 2), H, m) + 0.2
+        p[:, 2] = rng.uniform(cfg["z_range"][0], cfg["z_range"][1], n)
+        p[:, 3] = rng.uniform(0.0, 1.0, n)
+        clouds.append(p[rng.permutation(n)])
+    fr = dict(points=clouds, poses=np.zeros((2, 3)), weights=synth.make_weights(synth.config("c1")))
+    with make_ctx(cfg, fr, max_points=max(n, 1)) as ctx:
+        for points in (clouds, clouds[::-1]):
+            run_frame(ctx, fr, points=points)
+            for k in range(2):
+                _check_pillars(ctx, cfg, points[k], k)
+                canvas = R.rtcc_get_tensor(ctx, R.RTCC_T_CANVAS, k, np.float32).reshape(H * W, -1)
+                pil = N.pillars(N.cell_ids(points[k], cfg), cfg["max_pts"])
+                pw = N.prepared_weights(cfg, fr["weights"])
+                ref = N.pfn_canvas(points[k], pil, pw["pfn_w"], pw["pfn_b"], cfg)
+                assert np.max(np.abs(canvas - ref.reshape(H * W, -1)), initial=0.0) <= 1e-5

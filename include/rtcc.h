@@ -423,11 +423,12 @@ RTCC_API rtcc_status rtcc_profile_nodes(rtcc_ctx *ctx, int32_t warmup, int32_t r
 /* Per-kernel-group GPU durations (ms) of the last frame, recorded when
  * opts.node_timing = 1.  For each agent k, in order: h2d, pillar (cell ids,
  * counting sort, segment), pfn_canvas, conv[0 .. L-1], up[0 .. S-1] (0 if
- * no upsampling; 0 each when multiscale = 1), warp (0 unless warp_in_branch
+ * no upsampling; 0 each when multiscale = 1; where one launch runs all of
+ * them, up[0] has its time), warp (0 unless warp_in_branch
  * = 1 and the agent's pose is not the identity, which needs no
  * resampling); then warp_fuse (or fuse; with multiscale = 1 the warp and
  * fusion of every scale and the upsampling of the fused maps), head,
- * decode, nms (0 if off).  Conv nodes, the branch warp and a one-kernel
+ * decode, nms (0 if off; with the write of the result to the host).  Conv nodes, the branch warp and a one-kernel
  * warp_fuse / fuse node are the execution time of their kernels (events
  * that bracket the kernels themselves); the other nodes span the stream
  * between events recorded around them, dispatch gaps included.  *n = number written; ms must hold

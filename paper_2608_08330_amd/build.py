@@ -31,6 +31,7 @@ HIP_SOURCES = [
     "kernels/pillar.hip",
     "kernels/igemm.hip",
     "kernels/conv_slices.hip",
+    "kernels/upsample.hip",
     "kernels/post.hip",
     "kernels/nms.hip",
     "nms_api.hip",

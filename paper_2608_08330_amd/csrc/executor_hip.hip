@@ -210,6 +210,15 @@ class HipExecutor : public Executor {
             HIP_TRY(kern::conv_frag(p.bf16, static_cast<const char *>(d_mat) + c.w_off * p.elt, d_frag_[l], c.Co, c.Ci,
                                     join_stream_));
         }
+        up_frag_.assign(p.ups.size(), nullptr);
+        up_fused_ = !p.ups.empty();
+        for (const UpLayer &u : p.ups) up_fused_ = up_fused_ && kern::upsample_fits(p.bf16, u.Ci, u.Co);
+        for (size_t i = 0; i < p.ups.size() && up_fused_; ++i) {
+            const UpLayer &u = p.ups[i];
+            HIP_TRY(alloc(&up_frag_[i], size_t(u.u) * u.u * u.Ci * u.Co * p.elt));
+            HIP_TRY(kern::upsample_frag(static_cast<const char *>(d_mat) + u.w_off * p.elt, up_frag_[i], u.u, u.Co, u.Ci,
+                                        join_stream_));
+        }
         HIP_TRY(hipDeviceSynchronize());
         return RTCC_OK;
     }
@@ -862,17 +871,14 @@ class HipExecutor : public Executor {
             if (timing) HIP_TRY(hipEventRecord(lead.ev[ev], s));
             ++ev;
         }
-        for (const UpLayer &u : p.ups) {
-            if (p.d.multiscale) break;  // upsampling runs once, on the fused maps
-            const void *in[kern::kMaxGroup];
+        if (!p.ups.empty() && !p.d.multiscale) {  // else upsampling runs once, on the fused maps
+            const void *in[RTCC_MAX_STAGES][kern::kMaxGroup];
             void *out[kern::kMaxGroup];
             for (int j = 0; j < m; ++j) {
-                in[j] = br_[agents[j]].d_act[p.stage_last_conv[u.stage]];
+                for (const UpLayer &u : p.ups) in[u.stage][j] = br_[agents[j]].d_act[p.stage_last_conv[u.stage]];
                 out[j] = br_[agents[j]].d_slotbuf;
             }
-            HIP_TRY(upsample(u, in, out, m, s));
-            if (timing) HIP_TRY(hipEventRecord(lead.ev[ev], s));
-            ++ev;
+            HIP_TRY(upsample(in, out, m, s, timing ? &lead.ev[ev] : nullptr));
         }
         if (p.d.warp_in_branch) {
             for (int j = 0; j < m; ++j) {
@@ -941,9 +947,46 @@ class HipExecutor : public Executor {
         return e;
     }
 
-    // Upsampling u of the map `in` into channels [c_off, c_off + Co) of `out`
-    // ([H2][W2][c_slot]).
-    hipError_t upsample(const UpLayer &u, const void *const *in, void *const *out, int m, hipStream_t s) {
+    // Every stage's upsampling of m maps (in[stage][map]) into its channels of
+    // `out` ([H2][W2][c_slot]): one launch over the stages where their shapes
+    // allow it, else one per stage.  done (NULL: none): an event per stage,
+    // recorded after its launch (after the one launch for all).
+    hipError_t upsample(const void *const (*in)[kern::kMaxGroup], void *const *out, int m, hipStream_t s,
+                        const hipEvent_t *done) {
+        const Plan &p = p_;
+        hipError_t e = hipSuccess;
+        if (up_fused_) {
+            kern::UpsampleArgs ua{};
+            ua.n_stages = int(p.ups.size());
+            ua.batch = m;
+            ua.Ho = p.H2;
+            ua.Wo = p.W2;
+            ua.Co = p.ups[0].Co;
+            ua.ldo = p.c_slot;
+            for (int i = 0; i < ua.n_stages; ++i) {
+                const UpLayer &u = p.ups[i];
+                kern::UpsampleStage &st = ua.stage[i];
+                st.wfrag = up_frag_[i];
+                st.bias = static_cast<const float *>(d_bias) + u.b_off;
+                st.Hi = u.Hi;
+                st.Wi = u.Wi;
+                st.Ci = u.Ci;
+                st.u = u.u;
+                st.c_off = u.c_off;
+                for (int j = 0; j < m; ++j) ua.in[i][j] = in[u.stage][j];
+            }
+            for (int j = 0; j < m; ++j) ua.out[j] = out[j];
+            e = kern::upsample(ua, s);
+        }
+        for (size_t i = 0; i < p.ups.size() && e == hipSuccess; ++i) {
+            if (!up_fused_) e = upsample_stage(p.ups[i], in[p.ups[i].stage], out, m, s);
+            if (e == hipSuccess && done) e = hipEventRecord(done[i], s);
+        }
+        return e;
+    }
+
+    // Upsampling u of the maps `in` into channels [c_off, c_off + Co) of `out`.
+    hipError_t upsample_stage(const UpLayer &u, const void *const *in, void *const *out, int m, hipStream_t s) {
         const Plan &p = p_;
         kern::GemmArgs ga{};
         ga.wt = static_cast<const char *>(d_mat) + u.w_off * p.elt;
@@ -985,7 +1028,8 @@ class HipExecutor : public Executor {
         const Plan &p = p_;
         if (p.d.multiscale) {
             // every scale: warp the K stage maps onto the stage's ego grid and
-            // fuse them, then upsample the fused map into the head's input
+            // fuse them; then upsample the fused maps into the head's input
+            const void *fin[RTCC_MAX_STAGES][kern::kMaxGroup];
             for (const UpLayer &u : p.ups) {
                 kern::WarpArgs wa{};
                 for (int k = 0; k < p.K; ++k) {
@@ -999,10 +1043,9 @@ class HipExecutor : public Executor {
                 wa.W2 = u.Wi;
                 wa.C = u.Ci;
                 HIP_TRY(kern::warp_fuse(p.bf16, p.d.fusion == RTCC_FUSE_ATTN, wa, s));
-                const void *fin = d_fused_stage_[u.stage];
-                void *fout = d_fused;
-                HIP_TRY(upsample(u, &fin, &fout, 1, s));
+                fin[u.stage][0] = d_fused_stage_[u.stage];
             }
+            HIP_TRY(upsample(fin, &d_fused, 1, s, nullptr));
         } else if (p.d.warp_in_branch) {
             kern::FuseArgs fa{};
             for (int k = 0; k < p.K; ++k) fa.maps[k] = br_[k].ego_map;
@@ -1332,6 +1375,8 @@ class HipExecutor : public Executor {
     std::vector<kern::ConvPlan> plans_;
     std::vector<void *> d_frag_;  // per conv layer: weights in fragment order (null: not used)
     int n_cu_ = 0;
+    std::vector<void *> up_frag_;  // per upsampling: weights in fragment order
+    bool up_fused_ = false;        // the upsamplings run as one launch
     void *d_fused = nullptr, *d_head = nullptr, *d_head_counts = nullptr, *d_rec = nullptr, *d_count = nullptr;
     int nms_max_ = 0;  // 0: no NMS
     void *d_nms_key = nullptr, *d_nms_order = nullptr, *d_nms_foot = nullptr, *d_nms_out = nullptr;

@@ -157,6 +157,29 @@ hipError_t conv_slices(bool bf16, const GemmArgs &a, hipStream_t s, hipEvent_t s
 // Bt [N][9 Ci] (N a multiple of 16) to the order conv_slices reads; as large.
 hipError_t conv_frag(bool bf16, const void *wt, void *out, int32_t N, int32_t Ci, hipStream_t s);
 
+// The upsamplings of several stages into their channels of the slot, one
+// launch over the stages and over `batch` maps (upsample.hip).
+struct UpsampleStage {
+    const void *wfrag;   // upsample_frag of the stage's weights
+    const float *bias;   // [Co]
+    int32_t Hi, Wi, Ci;  // input map
+    int32_t u, c_off;    // kernel = stride; first output channel in the slot
+    int32_t per, blocks; // set by upsample
+};
+struct UpsampleArgs {
+    UpsampleStage stage[4];
+    const void *in[4][16];  // per stage and map
+    void *out[16];          // per map [Ho][Wo][ldo]
+    int32_t n_stages, batch, Ho, Wo, Co, ldo;
+};
+// Whether upsample runs a stage of this shape (else: deconv).
+inline bool upsample_fits(bool bf16, int Ci, int Co) {
+    return bf16 && (Ci == 64 || Ci == 128 || Ci == 256) && Co % 128 == 0;
+}
+hipError_t upsample(UpsampleArgs a, hipStream_t s);
+// u * u phases of Bt [Co][Ci] to the order upsample reads; as large.
+hipError_t upsample_frag(const void *wt, void *out, int32_t u, int32_t Co, int32_t Ci, hipStream_t s);
+
 // ------------------------------------------------------------ post-join
 struct WarpArgs {
     const void *slots[16];  // per agent [H2*W2][C]

@@ -1,0 +1,205 @@
+// The transposed-conv upsamplings (kernel = stride = u) of a map's stages
+// into its slot, all of them in one launch (bf16, 64 / 128 / 256 input
+// channels, 128 k output channels; other shapes take the implicit GEMM).
+//
+// GEMM view: M = input pixels, K = C_in, and one group of 128 output channels
+// per phase (py, px) of the u x u kernel.  A block owns 64 input pixels and
+// st.per consecutive groups.  It stages its pixels, all channels, in LDS with
+// one burst and one barrier; each of its four wavefronts computes 64 pixels x
+// 32 channels of every group, weights loaded straight into registers half a
+// group ahead from a fragment-ordered copy (upsample_frag).  In that copy a
+// fragment pair's channels are interleaved so that a lane ends with 8
+// consecutive channels of a pixel: it stores 16 bytes, a wavefront 64
+// consecutive bytes per pixel, and no output goes through LDS.
+//
+// What bounds it: at 8 maps of 256 x 256 pixels (128 / 256 / 256 channels) the
+// bytes, 403 MB written and 218 MB read, 124 us at the rate of a large copy;
+// on small maps, latency and launches.  The implicit GEMM it replaces
+// (launches of their own, an LDS ring with a barrier per 32 channels, the
+// tile stored through LDS) is limited by LDS traffic at u > 1.  us, before ->
+// now, all three stages:
+//   one map   50 x 176 20.1 -> 6.2   22 x 30 18.5 -> 4.6   256 x 256 35 -> 24
+//   batches   6 x (50 x 176) 30 -> 20   3 x (128 x 128) 29.5 -> 17.6
+//             8 x (256 x 256) 190 -> 162
+// The steps are fenced for the scheduler: left alone it hoists every LDS read
+// and weight load (248 instead of 146 registers, two instead of three blocks
+// per CU; 8 x (256 x 256) 177 against 162 us with per = 4).
+// The K order is that of the implicit GEMM: the same bits.
+#include "kernels.hpp"
+
+#include "mfma.hpp"
+
+namespace rtcc {
+namespace kern {
+
+namespace {
+
+typedef unsigned int u32x4_t __attribute__((ext_vector_type(4)));
+
+constexpr int kPx = 64, kFM = kPx / 16;
+
+// Groups [g0, g1) of the block's pixels; KT = C_in / 32.
+template <int KT>
+__device__ inline void up_tile(const UpsampleArgs &a, const UpsampleStage &st, const uint16_t *in, uint16_t *out,
+                               int m0, int g0, int g1, unsigned char *smem) {
+    constexpr int KH = KT < 4 ? KT : 4, NH = KT / KH;  // weights in flight: KH steps
+    constexpr int GROUP = 4 * KT * 2 * 64;             // vectors of a group's weights
+    const uint32_t lds_base = lds_address(smem);
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int M = st.Hi * st.Wi;
+    // vector v of pixel row r of a 32-channel chunk sits at v ^ ((r >> 1) & 3)
+    for (int q = wave; q < KT * kFM; q += 4) {
+        const int c = q / kFM, blk = q - c * kFM;
+        const int row = blk * 16 + (lane >> 2);
+        const int vec = (lane & 3) ^ ((row >> 1) & 3);
+        const int m = m0 + row < M ? m0 + row : M - 1;  // not stored
+        load_lds16(in + size_t(m) * (KT * 32) + c * 32 + vec * 8, lds_base + (c * kPx + blk * 16) * 64);
+    }
+    const int fr = lane & 15, fk = lane >> 4;
+    const uint4 *wf = static_cast<const uint4 *>(st.wfrag) + size_t(g0) * GROUP + wave * (KT * 2 * 64) + lane;
+    uint4 w[2][KH][2];
+    auto load_w = [&](uint4 (&v)[KH][2], const uint4 *p) {
+#pragma unroll
+        for (int k = 0; k < KH; ++k)
+#pragma unroll
+            for (int j = 0; j < 2; ++j) v[k][j] = p[(k * 2 + j) * 64];
+    };
+    load_w(w[0], wf);
+    // output position of phase (0, 0) and LDS offset of the lane's pixels
+    int oy[kFM], ox[kFM], at[kFM];
+#pragma unroll
+    for (int i = 0; i < kFM; ++i) {
+        const int r = i * 16 + fr, m = m0 + r, iy = m / st.Wi;
+        oy[i] = m < M ? iy * st.u : a.Ho;
+        ox[i] = (m - iy * st.Wi) * st.u;
+        at[i] = r * 64 + ((fk ^ ((r >> 1) & 3)) << 4);
+    }
+    const int blocks128 = a.Co >> 7;
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // this wavefront's part of the pixels is in LDS
+    __syncthreads();
+    for (int g = g0; g < g1; ++g) {
+        const int phase = g / blocks128, n = (g - phase * blocks128) * 128 + wave * 32 + fk * 8;
+        const float4 b0 = *reinterpret_cast<const float4 *>(st.bias + n);
+        const float4 b1 = *reinterpret_cast<const float4 *>(st.bias + n + 4);
+        f32x4_t acc[kFM][2];
+#pragma unroll
+        for (int i = 0; i < kFM; ++i) acc[i][0] = acc[i][1] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+        uint4 x[2][kFM];
+        auto read = [&](int k, uint4 (&v)[kFM]) {
+#pragma unroll
+            for (int i = 0; i < kFM; ++i) v[i] = *reinterpret_cast<const uint4 *>(smem + k * (kPx * 64) + at[i]);
+        };
+        read(0, x[0]);
+#pragma unroll
+        for (int h = 0; h < NH; ++h) {
+            // this group's next half, or the next group's first
+            if (h + 1 < NH) load_w(w[(h + 1) & 1], wf + (h + 1) * (KH * 2 * 64));
+            else if (g + 1 < g1) load_w(w[NH & 1], wf + GROUP);
+#pragma unroll
+            for (int k = 0; k < KH; ++k) {
+                const int s = h * KH + k;
+                if (s + 1 < KT) read(s + 1, x[(s + 1) & 1]);
+#pragma unroll
+                for (int i = 0; i < kFM; ++i) {
+                    acc[i][0] = Step<uint16_t>::mma(w[h & 1][k][0], x[s & 1][i], acc[i][0]);
+                    acc[i][1] = Step<uint16_t>::mma(w[h & 1][k][1], x[s & 1][i], acc[i][1]);
+                }
+                __builtin_amdgcn_sched_barrier(0);
+            }
+        }
+        if constexpr (NH == 1) {
+#pragma unroll
+            for (int k = 0; k < KH; ++k)
+#pragma unroll
+                for (int j = 0; j < 2; ++j) w[0][k][j] = w[1][k][j];
+        }
+        wf += GROUP;
+        const int py = phase / st.u, px = phase - py * st.u;
+#pragma unroll
+        for (int i = 0; i < kFM; ++i) {
+            const int y = oy[i] + py, xx = ox[i] + px;
+            if (y >= a.Ho || xx >= a.Wo) continue;
+            const f32x4_t p = acc[i][0], q = acc[i][1];
+            const u32x4_t o = {pack_bf16(fmaxf(p[0] + b0.x, 0.f), fmaxf(p[1] + b0.y, 0.f)),
+                               pack_bf16(fmaxf(p[2] + b0.z, 0.f), fmaxf(p[3] + b0.w, 0.f)),
+                               pack_bf16(fmaxf(q[0] + b1.x, 0.f), fmaxf(q[1] + b1.y, 0.f)),
+                               pack_bf16(fmaxf(q[2] + b1.z, 0.f), fmaxf(q[3] + b1.w, 0.f))};
+            // read by the next kernel, past the L2
+            __builtin_nontemporal_store(
+                o, reinterpret_cast<u32x4_t *>(out + (size_t(y) * a.Wo + xx) * a.ldo + st.c_off + n));
+        }
+    }
+}
+
+__global__ __launch_bounds__(256, 2) void k_upsample(UpsampleArgs a) {
+    __shared__ __attribute__((aligned(1024))) unsigned char smem[kPx * 256 * 2];
+    // each XCD takes a contiguous run of blocks; map bt's blocks are one run
+    int bid = blockIdx.x;
+    const int nbx = gridDim.x;
+    if ((nbx & 7) == 0) bid = (bid & 7) * (nbx >> 3) + (bid >> 3);
+    const int per_map = nbx / a.batch;
+    const int bt = bid / per_map;
+    bid -= bt * per_map;
+    int s = 0;
+    while (bid >= a.stage[s].blocks) bid -= a.stage[s++].blocks;
+    const UpsampleStage &st = a.stage[s];
+    const int groups = st.u * st.u * (a.Co >> 7);
+    const int runs = (groups + st.per - 1) / st.per;  // blocks per 64 pixels
+    const int m0 = bid / runs * kPx, g0 = bid % runs * st.per;
+    const int g1 = g0 + st.per < groups ? g0 + st.per : groups;
+    const uint16_t *in = static_cast<const uint16_t *>(a.in[s][bt]);
+    uint16_t *out = static_cast<uint16_t *>(a.out[bt]);
+    if (st.Ci == 64) up_tile<2>(a, st, in, out, m0, g0, g1, smem);
+    else if (st.Ci == 128) up_tile<4>(a, st, in, out, m0, g0, g1, smem);
+    else up_tile<8>(a, st, in, out, m0, g0, g1, smem);
+}
+
+// Bt [u * u phases][Co][Ci] to [phase][128 channels][wavefront][step][j][lane]:
+// lane (fr, fk) of fragment j holds vector fk of channel 32 wavefront + 8 (fr /
+// 4) + 4 j + fr % 4, so that rows 4 fk .. 4 fk + 3 of the pair's products are
+// channels 8 fk .. 8 fk + 7.
+__global__ __launch_bounds__(256) void k_upsample_frag(const uint16_t *wt, uint4 *out, int groups, int KT) {
+    const int total = groups * 4 * KT * 2 * 64;
+    for (int v = blockIdx.x * 256 + threadIdx.x; v < total; v += gridDim.x * 256) {
+        const int lane = v & 63, j = (v >> 6) & 1, k = (v >> 7) % KT, gw = (v >> 7) / KT;
+        const int fr = lane & 15, fk = lane >> 4;
+        const int n = gw * 32 + 8 * (fr >> 2) + 4 * j + (fr & 3);
+        out[v] = *reinterpret_cast<const uint4 *>(wt + size_t(n) * KT * 32 + k * 32 + fk * 8);
+    }
+}
+
+}  // namespace
+
+hipError_t upsample_frag(const void *wt, void *out, int32_t u, int32_t Co, int32_t Ci, hipStream_t s) {
+    if (!upsample_fits(true, Ci, Co)) return hipErrorInvalidValue;
+    k_upsample_frag<<<256, 256, 0, s>>>(static_cast<const uint16_t *>(wt), static_cast<uint4 *>(out), u * u * (Co >> 7),
+                                        Ci / 32);
+    return hipGetLastError();
+}
+
+hipError_t upsample(UpsampleArgs a, hipStream_t s) {
+    // One group per block, for the shortest chain, until the blocks are many
+    // times what runs at once; then four, so that the pixels are staged for
+    // four phases (8 x (256 x 256): 24,576 blocks 175, four groups 162 us; one
+    // 256 x 256 map, 3,072 blocks, 24 against 37)
+    int64_t single = 0;
+    for (int q = 0; q < a.n_stages; ++q) {
+        const UpsampleStage &st = a.stage[q];
+        if (!upsample_fits(true, st.Ci, a.Co)) return hipErrorInvalidValue;
+        single += int64_t((st.Hi * st.Wi + kPx - 1) / kPx) * st.u * st.u * (a.Co >> 7);
+    }
+    const int per = single * a.batch > 8192 ? 4 : 1;
+    int64_t blocks = 0;
+    for (int q = 0; q < a.n_stages; ++q) {
+        UpsampleStage &st = a.stage[q];
+        const int groups = st.u * st.u * (a.Co >> 7);
+        st.per = per < groups ? per : groups;
+        st.blocks = (st.Hi * st.Wi + kPx - 1) / kPx * ((groups + st.per - 1) / st.per);
+        blocks += st.blocks;
+    }
+    k_upsample<<<unsigned(blocks * a.batch), 256, 0, s>>>(a);
+    return hipGetLastError();
+}
+
+}  // namespace kern
+}  // namespace rtcc

@@ -3,7 +3,8 @@ channel width (two slices, four, four of two chunks), both strides, float32
 and bf16, on grids with ragged tiles, one map per launch (two-row tiles) and
 eight maps per launch (the larger tiles).  Every layer elementwise against the
 oracle convolution of its GPU input, and the group launch bit for bit equal to
-separate launches (the tiles sum in the same order)."""
+separate launches (the tiles sum in the same order).  The upsamplings of the
+same networks (one launch for all stages, or one each) likewise."""
 
 import copy
 
@@ -24,6 +25,8 @@ SHAPES = [
     ("one_row", "bf16", 128, ((2, 64, 2),), 128, (1, 33)),
     ("narrow", "bf16", 64, ((1, 96, 1), (2, 32, 1)), 128, (67, 131)),        # 96 channels: no 64-channel tiles
     ("deep_entry", "bf16", 256, ((2, 96, 1), (1, 64, 1)), 64, (66, 127)),    # stride 2 at 256 channels
+    ("upsample", "bf16", 64, ((1, 64, 1), (2, 128, 1), (2, 256, 1)), 128, (35, 53)),  # x1, x2, x4 with a crop
+    ("wide_up", "bf16", 64, ((2, 128, 1), (2, 256, 1)), 256, (30, 46)),      # two blocks of 128 output channels
     ("fp32", "fp32", 64, ((2, 32, 2),), 32, (47, 95)),
 ]
 
@@ -79,5 +82,7 @@ def test_slices_against_the_oracle_and_between_batch_sizes(name, precision, c_pf
                 check_conv_layers(ctx, cfg, pw, k)
             got.append([R.rtcc_get_tensor(ctx, R.RTCC_T_CONV_OUT, (l << 8) | k, np.uint8)
                         for l in range(n_layers) for k in range(cfg["K"])])
+            if up:
+                got[-1] += [R.rtcc_get_tensor(ctx, R.RTCC_T_SLOT, k, np.uint8) for k in range(cfg["K"])]
         for a, b in zip(*got):
             assert np.array_equal(a, b)

@@ -27,6 +27,8 @@ SHAPES = [
     ("deep_entry", "bf16", 256, ((2, 96, 1), (1, 64, 1)), 64, (66, 127)),    # stride 2 at 256 channels
     ("upsample", "bf16", 64, ((1, 64, 1), (2, 128, 1), (2, 256, 1)), 128, (35, 53)),  # x1, x2, x4 with a crop
     ("wide_up", "bf16", 64, ((2, 128, 1), (2, 256, 1)), 256, (30, 46)),      # two blocks of 128 output channels
+    # eight maps: more blocks than the one-group upsampling takes, 64 / 128 / 256 input channels
+    ("many_up", "bf16", 64, ((1, 64, 1), (2, 128, 1), (2, 256, 1)), 128, (197, 203)),
     ("fp32", "fp32", 64, ((2, 32, 2),), 32, (47, 95)),
 ]
 

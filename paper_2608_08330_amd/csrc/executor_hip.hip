@@ -267,6 +267,20 @@ class HipExecutor : public Executor {
         return e;
     }
 
+    // Points of a group of m up to which a kernel on the group's stream reads
+    // them from pinned memory; beyond, a DMA copy per agent.  The kernel saves
+    // the host a copy, an event and a wait per agent and the stream the hand
+    // over from the copy engine, but its reads share the bus with, and hold up,
+    // what runs beside it.  A frame, us, copies -> kernel, points per agent:
+    //   8 alone   24,000 675 -> 680   40,000 697 -> 729   100,000 760 -> 960
+    //   1 alone    8,000 257 -> 252   24,000 261 -> 257    40,000 274 -> 272
+    //   group of 8 8,000 496 -> 412   24,000 506 -> 463    40,000 530 -> 527
+    //   group of 4 8,000 364 -> 321   24,000 371 -> 345    60,000 421 -> 425
+    //   SERIAL, 8  8,000 535 -> 412   24,000 578 -> 464   100,000 808 -> 733
+    static int64_t upload_points(int m, bool serial) {
+        return int64_t(m) * (m == 1 ? 24576 : serial ? 131072 : 40000);
+    }
+
     rtcc_status dispatch(const DispatchItem *items, int m, std::string &err) override {
         HIP_TRY(hipSetDevice(dev_));
         if (m < 1 || m > kern::kMaxGroup) {
@@ -279,6 +293,11 @@ class HipExecutor : public Executor {
         // the group's encoders run on the first member's stream
         hipStream_t ls = serial ? join_stream_ : lead.stream;
         int agents[kern::kMaxGroup];
+        kern::PointsUpload up{};  // the inputs that one kernel copies
+        int64_t host_pts = 0;
+        for (int j = 0; j < m; ++j)
+            if (!items[j].device_src) host_pts += items[j].n;
+        const bool one_upload = !timing && host_pts <= upload_points(m, serial);
         for (int j = 0; j < m; ++j) {
             const DispatchItem &it = items[j];
             agents[j] = it.agent;
@@ -289,7 +308,11 @@ class HipExecutor : public Executor {
             const float *src = it.pts;
             if (!it.device_src) {
                 src = static_cast<const float *>(b.d_pts);
-                if (it.n > 0) {
+                if (one_upload && it.n > 0) {
+                    up.src[up.m] = reinterpret_cast<const float4 *>(b.staging);
+                    up.dst[up.m] = static_cast<float4 *>(b.d_pts);
+                    up.n[up.m++] = int32_t(it.n);
+                } else if (it.n > 0) {
                     // the member's own stream (the lead's is ls), or in
                     // SERIAL mode the transfer stream
                     HIP_TRY(hipMemcpyAsync(b.d_pts, b.staging, size_t(it.n) * 16, hipMemcpyHostToDevice,
@@ -302,7 +325,7 @@ class HipExecutor : public Executor {
             }
             // ls runs after the member's input copy on the member's stream
             // (the stream holds no other work of the frame)
-            if (bs != ls && !it.device_src && it.n > 0) {
+            if (bs != ls && !it.device_src && it.n > 0 && !one_upload) {
                 HIP_TRY(hipEventRecord(b.h2d_done, bs));
                 HIP_TRY(hipStreamWaitEvent(ls, b.h2d_done, 0));
             }
@@ -311,6 +334,7 @@ class HipExecutor : public Executor {
             b.host_input = !it.device_src;
             HIP_TRY(prepare_branch(b, ls));
         }
+        if (up.m > 0) HIP_TRY(kern::points_upload(up, ls));
         // ... and (from its second launch on) after the frame's canvas clear
         // (in stream order when the clear was enqueued on this stream)
         hipEvent_t clear_ev = clear_pending_ && clear_stream_ != ls ? ev_clear_ : nullptr;

@@ -60,6 +60,15 @@ struct PillarGroup {
     int32_t tile_cells; // kTileCells or kTileCellsFine
 };
 
+// The points of m agents from pinned host memory to device memory, one launch.
+struct PointsUpload {
+    const float4 *src[kMaxGroup];
+    float4 *dst[kMaxGroup];
+    int32_t n[kMaxGroup];
+    int32_t m;
+};
+hipError_t points_upload(const PointsUpload &u, hipStream_t s);
+
 // Points from which on a pillar is crowded: above the cap, and above a few.
 inline int32_t pfn_crowd(int32_t max_pts) { return max_pts < 4 ? max_pts : 4; }
 

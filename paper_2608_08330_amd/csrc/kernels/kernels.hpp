@@ -91,9 +91,17 @@ hipError_t bin_count(const PillarGroup &grp, const PillarGeom &g, hipStream_t s)
 hipError_t bin_scatter(const PillarGroup &grp, hipStream_t s);
 hipError_t tile_sort(const PillarGroup &grp, int32_t crowd, hipStream_t s);
 // K1 to K3 in one launch, one block per agent, for small inputs: the same
-// lists, member and sorted points.
-constexpr int kSmallPoints = 16384, kSmallCells = 65536;
-inline bool pillars_small_fits(int n_cells, int n_max) { return n_cells <= kSmallCells && n_max <= kSmallPoints; }
+// lists, member and sorted points.  Two launches fewer, about 10 us of the host
+// per release that is not a graph, against a kernel that grows with the points
+// and cells of one agent.  A frame, us, one block -> three launches:
+//   64 x 64 cells, four releases   2,000 points 172 -> 196, 8,000 198 -> 212;
+//     as graphs, a group of four   2,000 123 -> 125, 8,000 151 -> 146
+//   352 x 100, four releases       4,000 413 -> 436, 8,000 422 -> 440;
+//     a group of eight             4,000 357 -> 356, 8,000 380 -> 366
+constexpr int kSmallPoints = 8192, kSmallCells = 16384;
+inline bool pillars_small_fits(int n_cells, int n_max) {
+    return n_cells <= kSmallCells ? n_max <= kSmallPoints : n_cells <= kSmallCells * 4 && n_max <= kSmallPoints / 2;
+}
 hipError_t pillars_small(const PillarGroup &grp, const PillarGeom &g, int32_t crowd, hipStream_t s);
 // K4 pfn_canvas: the dense canvas [H*W][C]: per pillar cell, channel max over the first
 // min(count, max_pts) members of ReLU(W^T f + b) (for cells over the cap,

@@ -36,7 +36,6 @@
 // segment, and every consumer of it is order-independent (max, set
 // selection), so every output is bitwise reproducible.
 #include <climits>
-#include <type_traits>
 
 #include "kernels.hpp"
 
@@ -332,15 +331,10 @@ __global__ __launch_bounds__(256) void k_tile_sort(const PillarGroup grp, int32_
     }
 }
 
-// The whole sort of one agent in one block: at most kSmallPoints points and
-// CELLS cells, two 16-bit counts (then offsets) per LDS word.  Bound by latency
-// and by what one CU can issue (16 wavefronts): the line is where it takes as
-// long as the three launches.  2,000 points on 4,096 cells 20 -> 10.8 us, 6,000
-// on 2,640 38 -> 16.5 (one launch for four); six agents with 4,000 points on
-// 35,200 cells each 19 -> 18.9.
-constexpr int kSmallPerThread = kSmallPoints / 1024;
-static_assert(kSmallPerThread == 16, "four runs of four points per thread");
-template <int CELLS>
+// The whole sort of one agent in one block: at most PER x 1024 points and
+// CELLS cells, two 16-bit counts (then offsets) per LDS word; the points stay
+// in registers.  Bound by latency and by what one CU can issue (16 wavefronts).
+template <int CELLS, int PER>
 __global__ __launch_bounds__(1024) void k_pillars_small(const PillarGroup grp, const PillarGeom g, int32_t crowd) {
     __shared__ uint32_t cnt[CELLS / 2];
     __shared__ int2 wsum[16];
@@ -352,32 +346,22 @@ __global__ __launch_bounds__(1024) void k_pillars_small(const PillarGroup grp, c
     const int words = (grp.n_cells + 1) / 2;
     for (int w = tid; w < words; w += 1024) cnt[w] = 0u;
     __syncthreads();
-    // four points of a thread at a time, their loads in flight together
-    int at[kSmallPerThread];  // cell + (rank in the cell << 16); -1: dropped
-    auto count4 = [&](auto first) {
-        constexpr int u0 = decltype(first)::value;
+    f32x4_t q[PER];
 #pragma unroll
-        for (int u = 0; u < 4; ++u) at[u0 + u] = -1;
-        if (u0 * 1024 >= n) return;
-        f32x4_t q[4];
+    for (int u = 0; u < PER; ++u) {
+        const int i = u * 1024 + tid;
+        q[u] = i < n ? pv[i] : f32x4_t{INFINITY, 0.f, 0.f, 0.f};  // no cell
+    }
+    int at[PER];  // cell + (rank in the cell << 16); -1: dropped
 #pragma unroll
-        for (int u = 0; u < 4; ++u) {
-            const int i = (u0 + u) * 1024 + tid;
-            q[u] = i < n ? pv[i] : f32x4_t{INFINITY, 0.f, 0.f, 0.f};  // no cell
+    for (int u = 0; u < PER; ++u) {
+        const int c = cell_of(make_float4(q[u].x, q[u].y, q[u].z, q[u].w), g);
+        at[u] = -1;
+        if (c >= 0) {
+            const int sh = (c & 1) * 16;
+            at[u] = c | int(((atomicAdd(&cnt[c >> 1], 1u << sh) >> sh) & 0xffffu) << 16);
         }
-#pragma unroll
-        for (int u = 0; u < 4; ++u) {
-            const int c = cell_of(make_float4(q[u].x, q[u].y, q[u].z, q[u].w), g);
-            if (c >= 0) {
-                const int sh = (c & 1) * 16;
-                at[u0 + u] = c | int(((atomicAdd(&cnt[c >> 1], 1u << sh) >> sh) & 0xffffu) << 16);
-            }
-        }
-    };
-    count4(std::integral_constant<int, 0>{});
-    count4(std::integral_constant<int, 4>{});
-    count4(std::integral_constant<int, 8>{});
-    count4(std::integral_constant<int, 12>{});
+    }
     __syncthreads();
     // an odd number of consecutive words per thread: no bank conflicts
     const int per = ((words + 1023) / 1024) | 1;
@@ -416,27 +400,14 @@ __global__ __launch_bounds__(1024) void k_pillars_small(const PillarGroup grp, c
         list(2 * w + 1, int(both >> 16));
     }
     __syncthreads();
-    auto place4 = [&](auto first) {
-        constexpr int u0 = decltype(first)::value;
-        if (u0 * 1024 >= n) return;
-        f32x4_t q[4];
 #pragma unroll
-        for (int u = 0; u < 4; ++u)
-            if (at[u0 + u] >= 0) q[u] = pv[(u0 + u) * 1024 + tid];
-#pragma unroll
-        for (int u = 0; u < 4; ++u) {
-            if (at[u0 + u] >= 0) {
-                const int c = at[u0 + u] & 0xffff;
-                const int d = int((cnt[c >> 1] >> ((c & 1) * 16)) & 0xffffu) + (at[u0 + u] >> 16);
-                B.member[d] = (u0 + u) * 1024 + tid;
-                reinterpret_cast<f32x4_t *>(B.sorted)[d] = q[u];
-            }
-        }
-    };
-    place4(std::integral_constant<int, 0>{});
-    place4(std::integral_constant<int, 4>{});
-    place4(std::integral_constant<int, 8>{});
-    place4(std::integral_constant<int, 12>{});
+    for (int u = 0; u < PER; ++u) {
+        if (at[u] < 0) continue;
+        const int c = at[u] & 0xffff;
+        const int d = int((cnt[c >> 1] >> ((c & 1) * 16)) & 0xffffu) + (at[u] >> 16);
+        B.member[d] = u * 1024 + tid;
+        reinterpret_cast<f32x4_t *>(B.sorted)[d] = q[u];
+    }
     if (tid == 0) {
         B.meta[0] = tot.x;
         B.meta[1] = tot.y & 0xffff;
@@ -703,8 +674,9 @@ hipError_t tile_sort(const PillarGroup &grp, int32_t crowd, hipStream_t s) {
 
 hipError_t pillars_small(const PillarGroup &grp, const PillarGeom &g, int32_t crowd, hipStream_t s) {
     if (!pillars_small_fits(grp.n_cells, grp.n_max)) return hipErrorInvalidValue;
-    if (grp.n_cells <= kSmallCells / 4) k_pillars_small<kSmallCells / 4><<<unsigned(grp.m), 1024, 0, s>>>(grp, g, crowd);
-    else k_pillars_small<kSmallCells><<<unsigned(grp.m), 1024, 0, s>>>(grp, g, crowd);
+    const unsigned blocks = unsigned(grp.m);
+    if (grp.n_cells <= kSmallCells) k_pillars_small<kSmallCells, kSmallPoints / 1024><<<blocks, 1024, 0, s>>>(grp, g, crowd);
+    else k_pillars_small<kSmallCells * 4, kSmallPoints / 2048><<<blocks, 1024, 0, s>>>(grp, g, crowd);
     return hipGetLastError();
 }
 

@@ -66,12 +66,14 @@ def test_fifteen_million_points_on_two_tiles():
         _check_pillars(ctx, cfg, fr["points"][1], 1)
 
 
-# (H, W) cells and points: one block per agent up to 16,384 points and 65,536
-# cells (its smaller form up to 16,384 cells), tiles of 512 cells up to 131,072
-# cells and of 2,048 above
+# (H, W) cells and points: one block per agent up to 8,192 points and 16,384
+# cells or 4,096 points and 65,536 cells, tiles of 512 cells up to 131,072 cells
+# and of 2,048 above
 @pytest.mark.parametrize("grid,n", [
     ((1, 1), 40), ((3, 5), 0), ((3, 5), 1), ((128, 128), 1024), ((128, 129), 1025), ((127, 129), 16384),
-    ((256, 256), 16384), ((256, 256), 16385), ((256, 257), 1023), ((11, 5958), 5000), ((512, 1), 513),
+    ((256, 256), 16384), ((256, 256), 16385), ((128, 128), 8192), ((128, 128), 8193),
+    ((128, 129), 4096), ((128, 129), 4097), ((256, 256), 4096), ((256, 257), 4096),
+    ((256, 257), 1023), ((11, 5958), 5000), ((512, 1), 513),
     ((256, 512), 20000), ((257, 511), 20000), ((2, 70001), 30000),
 ])
 def test_sizes_at_the_edges_of_the_paths(grid, n):

@@ -620,6 +620,9 @@ class HipExecutor : public Executor {
             if (p_.d.warp_in_branch && b.warp_ran) HIP_TRY(hipEventElapsedTime(&v, b.wev[0], b.wev[1]));
             ms[q++] = v;
         }
+        // the join ends at the flag that the last kernel sets; the event behind
+        // that kernel may still be open
+        HIP_TRY(hipEventSynchronize(post_ev_[4]));
         for (int e = 0; e < 4; ++e) {
             float v = 0.f;
             HIP_TRY(hipEventElapsedTime(&v, post_ev_[e], post_ev_[e + 1]));
@@ -1153,8 +1156,8 @@ class HipExecutor : public Executor {
     }
 
     // The points each pillar of the agent's last frame fed to the PFN: the
-    // first min(count, cap) entries of its member segment (the overfull
-    // selection moved the lowest indices there), sorted per pillar, pillars
+    // first min(count, cap) entries of its member segment (the point-feature
+    // net moved the lowest indices there), sorted per pillar, pillars
     // in ascending cell order.
     rtcc_status used_members(int agent, std::vector<int32_t> &out, std::string &err) {
         if (agent < 0 || agent >= p_.K) {

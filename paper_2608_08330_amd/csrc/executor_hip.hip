@@ -429,7 +429,8 @@ class HipExecutor : public Executor {
         // one-kernel fusion nodes are timed by events bracketing the kernel
         if (timing && p_.d.multiscale) HIP_TRY(hipEventRecord(post_ev_[0], js));
         rtcc_status s;
-        // the export kernel at the end of the post-join work sets this flag;
+        // the last kernel of the post-join work sets this flag (the selection,
+        // or the export of a frame without suppression);
         // every export enqueued before has completed (joins wait for theirs,
         // node profiling synchronises)
         __atomic_store_n(static_cast<uint32_t *>(h_export) + 2, 0u, __ATOMIC_RELAXED);
@@ -760,9 +761,9 @@ class HipExecutor : public Executor {
 
     hipStream_t compute_stream_for_join() const { return join_stream_; }
 
-    // Until the export kernel of this join has set word 2 of h_export to 1
+    // Until the last kernel of this join has set word 2 of h_export to 1
     // (acquire).  A stream error ends the wait with that error; a stream
-    // that completes without the store (no export kernel ran) is an
+    // that completes without the store (it did not run) is an
     // internal error.
     rtcc_status wait_export(hipStream_t s, std::string &err) {
         const uint32_t *w = static_cast<const uint32_t *>(h_export) + 2;

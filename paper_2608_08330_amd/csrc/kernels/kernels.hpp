@@ -270,7 +270,7 @@ hipError_t export_results(const int32_t *count, const float *recs, int first, vo
 
 // Rotated NMS of the decoded records (see nms.hip).
 constexpr int kNmsMaxCandidates = 16384;
-constexpr int kNmsFootDoubles = 8;  // per candidate: x, y, w, l, cos yaw, sin yaw, valid, circumradius
+constexpr int kNmsFootDoubles = 8;  // per candidate: x, y, w, l, cos yaw, sin yaw, valid (0, 1, 2), circumradius
 // Ranking key of a score: its order-preserving image.  Flips the sign bit of
 // a non-negative float and every bit of a negative one, which orders all
 // finite and infinite values like the numbers (-0 is taken as +0); a NaN, and

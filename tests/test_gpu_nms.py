@@ -8,6 +8,7 @@ import sys
 import numpy as np
 import pytest
 
+from oracle import nms as ONMS
 from paper_2608_08330_amd import rtcc as R
 from tests.helpers import check_nms
 
@@ -162,6 +163,71 @@ def test_shared_edges_and_nearly_parallel_edges():
     anchors = np.arange(n, dtype=np.int32) * 3
     for thr in (0.15, 0.5):
         _check(boxes, scores, anchors, 4096, thr, "grid thr %g" % thr)
+
+
+@pytest.mark.parametrize("w,l", [(1e-20, 2e-20), (1e20, 2e20), (3e-7, 5e-7), (2e6, 3e6), (0.05, 3.3), (1.0, 1.0)])
+def test_sides_of_any_size(w, l):
+    """Overlapping boxes whose areas, or products of four lengths, leave the
+    float32 range, next to sizes that the float32 evaluation is trusted with."""
+    rng = np.random.default_rng(41)
+    n = 200
+    boxes = np.zeros((n, 7), dtype=np.float32)
+    boxes[:, 0:2] = rng.normal(0.0, max(w, l / 8), (n, 2))
+    boxes[:, 3] = w * rng.uniform(0.8, 1.2, n)
+    boxes[:, 4] = l * rng.uniform(0.8, 1.2, n)
+    boxes[:, 5] = 1.5
+    boxes[:, 6] = rng.uniform(-math.pi, math.pi, n)
+    scores = rng.uniform(0.3, 1.0, n).astype(np.float32)
+    kept = _check(boxes, scores, np.arange(n, dtype=np.int32), 4096, 0.15, "sides %g x %g" % (w, l))
+    assert 0 < kept < n
+
+
+@pytest.mark.parametrize("w,l", [(1.6, 3.9), (3.9, 1.6), (1.0, 1.0), (0.1, 6.0)])
+def test_equal_boxes_slid_along_their_heading(w, l):
+    """Pairs of equal boxes, one slid along the heading: two pairs of edges
+    are collinear up to the rounding of the centres."""
+    rng = np.random.default_rng(44)
+    wrong = []
+    for _ in range(200):
+        yaw = rng.uniform(-math.pi, math.pi)
+        boxes = np.zeros((2, 7), dtype=np.float32)
+        boxes[:, 0:2] = rng.uniform(-1.0, 1.0, 2)
+        boxes[1, 0:2] += rng.uniform(-0.9, 0.9) * l * np.array([math.cos(yaw), math.sin(yaw)])
+        boxes[:, 3], boxes[:, 4], boxes[:, 6] = w, l, yaw
+        v = ONMS.iou(boxes[0].astype(np.float64), boxes[1].astype(np.float64))
+        rec = _records(boxes, np.array([0.9, 0.8], np.float32), [0, 1])
+        for thr in (0.15, 0.5, 0.8):
+            if len(_gpu_nms(rec, 64, thr)) != (1 if v > float(np.float32(thr)) else 2):
+                wrong.append((v, thr))
+    assert not wrong, (len(wrong), wrong[:5])
+
+
+@pytest.mark.parametrize("w,l", [(0.001, 20.0), (0.003, 50.0), (0.31, 20.0)])
+def test_thin_boxes_at_their_own_threshold(w, l):
+    """Pairs of thin boxes, each against thresholds 3e-4 of its own IoU below
+    and above it (far more than float64 rounds, far less than float32 does at
+    aspect ratios of 20,000)."""
+    rng = np.random.default_rng(43)
+    wrong = tried = 0
+    while tried < 300:
+        boxes = np.zeros((2, 7), dtype=np.float32)
+        boxes[:, 0] = rng.uniform(-0.3 * l, 0.3 * l, 2)
+        boxes[:, 1] = rng.uniform(-0.5 * w, 0.5 * w, 2)
+        boxes[:, 3] = w * rng.uniform(0.7, 1.3, 2)
+        boxes[:, 4] = l * rng.uniform(0.7, 1.3, 2)
+        boxes[:, 6] = rng.uniform(-0.5, 0.5, 2) * w / l
+        turn = rng.uniform(-math.pi, math.pi)
+        c, s = math.cos(turn), math.sin(turn)
+        boxes[:, 0:2] = boxes[:, 0:2].astype(np.float64) @ np.array([[c, s], [-s, c]])
+        boxes[:, 6] += np.float32(turn)
+        v = ONMS.iou(boxes[0].astype(np.float64), boxes[1].astype(np.float64))
+        if not 0.01 < v < 0.99:
+            continue
+        tried += 1
+        rec = _records(boxes, np.array([0.9, 0.8], np.float32), [0, 1])
+        wrong += len(_gpu_nms(rec, 64, v * (1 - 3e-4))) != 1
+        wrong += len(_gpu_nms(rec, 64, v * (1 + 3e-4))) != 2
+    assert wrong == 0, (wrong, 2 * tried)
 
 
 def test_negative_and_signed_zero_scores():

@@ -538,6 +538,7 @@ constexpr int kSelectWaves = kSelectThreads / 64;
 constexpr int kMaxChunks = kNmsMaxCandidates / 64;
 constexpr int kSelCap = 8192;    // listed words held in LDS
 constexpr int kSupLds = 4096;    // candidates whose in-chunk suppressors are held in LDS
+constexpr int kWindow = 32;      // chunks in work at a time, two per wavefront
 constexpr int kFlagBits = 131072;  // records compacted per pass
 
 // Exclusive scan of one int per thread over the block; *total to everyone.
@@ -563,27 +564,37 @@ __device__ inline int select_scan(int v, int *wsum, int *total) {
 }
 
 // The greedy selection: kept(q) = no kept(p) with p ranked before q that
-// suppresses it.  All chunks of 64 rows iterate at once, a wavefront per
-// chunk: the rows removed from outside are the OR of the words listed for the
-// chunk whose row is kept in the current estimate, and the chunk then
-// resolves itself exactly (resolve_chunk_parallel), in place.  After t rounds
-// chunks 0 .. t - 1 are final, whatever the start and whichever of the other
-// chunks' words a wavefront still saw, so the rounds end, at the latest after
-// one per chunk, at the one fixed point (a round that changes nothing has read
-// only the words it leaves); scenes converge in a few.  A walk over the chunks
-// in order paid the same latency once per chunk.
+// suppresses it.  A window of chunks of 64 rows iterates at once, a wavefront
+// per chunk: the rows removed from outside are the OR of the words listed for
+// the chunk whose row is kept in the current estimate, and the chunk then
+// resolves itself exactly (resolve_chunk_parallel), in place.  A round in
+// which chunk l is the first to change has read only unchanged words for every
+// chunk up to l, which therefore are final, whichever of the other chunks'
+// words a wavefront saw: the window moves on behind l, or, after a round that
+// changes nothing, behind its end.  Every round moves it, so there are at most
+// as many rounds as chunks, of two chunks per wavefront; scenes take a few per
+// window.  A chunk that its suppressors leave as they did is not resolved
+// again.  A walk over the chunks in order paid the same latency once per
+// chunk; all chunks in every round are up to T^2 / 16 resolutions in a row.  The
+// call, us, walk -> all chunks -> window:
+//   a chain of boxes, each decided by the one before
+//                     1,500 212 -> 261 -> 177   4,096 430 -> 1,286 -> 376   16,384 2,104 -> 17,408 -> 1,564
+//   crowded           1,500 224 -> 108 -> 106   4,096 546 -> 182 -> 162     16,384 4,481 -> 1,304 -> 795
+// (the last with the mask kernel's changes).  Windows of 16 and 64 chunks: 349
+// and 398 for the chain of 4,096, 170 and 172 for the crowd.
 // The listed words are copied into LDS when they fit, else read where they
 // are.  The kept records are then compacted in ascending record order.
 // 1,400 records 16.6 us, 4,096 candidates of 30,000 crowded ones 45 us; as a
 // walk, with the kept records found by a scan over all records: 32.6 and 221.
 __global__ __launch_bounds__(kSelectThreads) void k_nms_select(NmsArgs a) {
-    __shared__ unsigned long long keep[kMaxChunks];
+    __shared__ unsigned long long keep[kMaxChunks], removed[kMaxChunks];
     __shared__ __attribute__((aligned(16))) unsigned long long eword[kSelCap];
     __shared__ unsigned short erow[kSelCap];
     __shared__ int coff[kMaxChunks + 1];
     __shared__ unsigned long long supl[kSupLds];
     __shared__ uint32_t fbits[kFlagBits / 32];
     __shared__ int wsum[kSelectWaves];
+    __shared__ int lowest[3];  // per round, the first chunk that changed
     static_assert(kSelCap * 8 >= kNmsMaxCandidates * 4, "the kept list reuses the words' LDS");
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int n = *a.count;
@@ -597,6 +608,7 @@ __global__ __launch_bounds__(kSelectThreads) void k_nms_select(NmsArgs a) {
     if (sup_lds)
         for (int q = tid; q < m; q += kSelectThreads) supl[q] = a.mask_t[q];
     for (int c = tid; c < T; c += kSelectThreads) keep[c] = ~0ull;
+    if (tid == 0) lowest[0] = T;
     __syncthreads();
     if (fits)
         for (int c = wave; c < T; c += kSelectWaves)
@@ -628,12 +640,16 @@ __global__ __launch_bounds__(kSelectThreads) void k_nms_select(NmsArgs a) {
         }
     }
     auto kept_row = [&](int r) { return (__hip_atomic_load(&keep[r >> 6], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP) >> (r & 63)) & 1ull; };
-    for (int it = 0; it < T; ++it) {
-        bool changed = false;
+    int first = 0, reached = 0;  // the first chunk not final, and not yet in work
+    for (int it = 0; first < T; ++it) {
+        const int end = first + kWindow < T ? first + kWindow : T;
+        int low = T;  // the first chunk of this wavefront that changed
         auto settle = [&](int c, unsigned long long rem, unsigned long long sup) {
             rem = wave_or64(rem);
+            if (c < reached && rem == removed[c]) return;
+            if (lane == 0) removed[c] = rem;
             const unsigned long long kb = resolve_chunk_parallel(rem, sup, m - c * 64 < 64 ? m - c * 64 : 64);
-            changed |= kb != keep[c];
+            if (kb != keep[c] && c < low) low = c;
             if (lane == 0) __hip_atomic_store(&keep[c], kb, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
         };
         auto listed_from = [&](int c, int k) {
@@ -648,7 +664,7 @@ __global__ __launch_bounds__(kSelectThreads) void k_nms_select(NmsArgs a) {
 #pragma unroll
         for (int g = 0; g < RC; ++g) {
             const int c = wave + g * kSelectWaves;
-            if (c >= T) continue;
+            if (c < first || c >= end) continue;
             unsigned long long rem = 0ull;
 #pragma unroll
             for (int x = 0; x < RE; ++x)
@@ -656,11 +672,18 @@ __global__ __launch_bounds__(kSelectThreads) void k_nms_select(NmsArgs a) {
             if (rlen[g] > 64 * RE) rem |= listed_from(c, lane + 64 * RE);
             settle(c, rem, rsup[g]);
         }
-        for (int c = wave + RC * kSelectWaves; c < T; c += kSelectWaves) {
+        // this wavefront's other chunks of the window
+        const int skip = first - wave > 0 ? (first - wave + kSelectWaves - 1) / kSelectWaves : 0;
+        for (int c = wave + (skip > RC ? skip : RC) * kSelectWaves; c < end; c += kSelectWaves) {
             const int row = c * 64 + lane;
             settle(c, listed_from(c, lane), row < m ? (sup_lds ? supl[row] : a.mask_t[row]) : 0ull);
         }
-        if (!__syncthreads_or(changed)) break;
+        if (lane == 0 && low < T) atomicMin(&lowest[it % 3], low);
+        if (tid == 0) lowest[(it + 1) % 3] = T;  // last read two rounds ago
+        __syncthreads();
+        const int l = lowest[it % 3];
+        first = l < T ? l + 1 : end;
+        reached = end;
     }
     // kept candidates -> their records, ascending: a bitmap of the records
     // per pass, its set bits numbered by a scan

@@ -105,6 +105,46 @@ def test_longest_chain():
         assert kept == (n + 1) // 2 or order[1] != 1
 
 
+@pytest.mark.parametrize("n", [2048, 2049, 4096, 16384])
+def test_long_chains(n):
+    """Chains as long as the selection's window of 32 chunks (2,048 boxes), one
+    box longer, and up to the largest candidate cap."""
+    boxes = np.zeros((n, 7), dtype=np.float32)
+    boxes[:, 0] = 3.0 * np.arange(n)
+    boxes[:, 3], boxes[:, 4], boxes[:, 5] = 1.6, 4.0, 1.5
+    scores = np.linspace(1.0, 0.3, n, dtype=np.float32)
+    print("nms chain n=%d" % n, flush=True)
+    for s, first in ((scores, 0), (scores[::-1], (n - 1) & 1)):
+        out = _gpu_nms(_records(boxes, s, np.arange(n)), n, 0.1)
+        assert np.array_equal(out[:, 8].copy().view(np.int32), np.arange(first, n, 2))
+
+
+def test_a_chain_takes_a_round_per_chunk():
+    """The selection of the longest chain (256 chunks, each decided by the one
+    before) next to that of as many boxes apart: about three times the call,
+    where evaluating every chunk in every round took 28 times."""
+    import time
+
+    import torch
+    n = 16384
+    times = []
+    for step in (12.0, 3.0):
+        boxes = np.zeros((n, 7), dtype=np.float32)
+        boxes[:, 0] = step * np.arange(n)
+        boxes[:, 3], boxes[:, 4], boxes[:, 5] = 1.6, 4.0, 1.5
+        rec = torch.from_numpy(_records(boxes, np.linspace(1.0, 0.3, n, dtype=np.float32), np.arange(n))).cuda()
+        out = torch.zeros((n, 9), dtype=torch.float32, device="cuda")
+        torch.cuda.synchronize()
+        t = []
+        for _ in range(7):
+            t0 = time.perf_counter()
+            R.rtcc_rotated_nms(rec.data_ptr(), n, n, 0.1, out.data_ptr())
+            t.append(time.perf_counter() - t0)
+        times.append(min(t[1:]))
+    print("nms chain: apart %.0f us, chain %.0f us" % (times[0] * 1e6, times[1] * 1e6), flush=True)
+    assert times[1] < 8 * times[0]
+
+
 def test_ties_identical_and_invalid_boxes():
     rng = np.random.default_rng(9)
     boxes, scores, anchors = _scene(rng, 300, 10.0, 5)

@@ -81,13 +81,33 @@ def test_random_scenes(seed, n, spread, clusters, cap, thr):
 
 @pytest.mark.parametrize("n,cap", [(63, 64), (64, 64), (65, 128), (511, 512), (513, 512), (1025, 1000), (131073, 200)])
 def test_counts_at_the_edges_of_tiles(n, cap):
-    """Record counts around the tiles of the ranking (64 records, eighths of
-    the keys), of the suppression matrix (64 x 64) and of the compaction (131,072
-    records per pass), scores of few values so that ties cross the tiles."""
+    """Record counts around the tiles of the ranking (64 records, sevenths of
+    the keys) and of the suppression matrix (64 x 64), scores of few values so
+    that ties cross the tiles."""
     rng = np.random.default_rng(n)
     boxes, scores, anchors = _scene(rng, n, 20.0 if n < 2000 else 400.0, max(1, min(n, 4000) // 6))
     scores = np.round(scores * 16).astype(np.float32) / 16
     _check(boxes, scores, anchors, cap, 0.15, "edge %d" % n)
+
+
+@pytest.mark.parametrize("n", [131072 + 31, 131072 + 700, 2 * 131072 + 5000])
+def test_candidates_in_every_compaction_pass(n):
+    """The kept records are compacted 131,072 records at a time: the highest
+    scores go to records at both ends of every pass and, as pairs of equal
+    boxes, to a record that another pass's suppresses."""
+    rng = np.random.default_rng(n)
+    boxes, scores, anchors = _scene(rng, n, 4000.0)
+    scores *= np.float32(0.5)
+    top = np.concatenate([np.r_[s:s + 90, e - 90:e] if e - s > 180 else np.arange(s, e)
+                          for s, e in ((s, min(n, s + 131072)) for s in range(0, n, 131072))])
+    scores[top] = rng.uniform(0.6, 1.0, len(top)).astype(np.float32)
+    boxes[top[:10]] = boxes[top[-10:]]
+    kept = _check(boxes, scores, anchors, len(top) + 40, 0.15, "passes %d" % n)
+    out = _gpu_nms(_records(boxes, scores, anchors), len(top) + 40, 0.15)
+    at = np.searchsorted(anchors, out[:, 8].copy().view(np.int32))
+    assert len(at) == kept
+    per_pass = np.bincount(at // 131072, minlength=-(-n // 131072))
+    assert (per_pass >= 20).all(), per_pass
 
 
 def test_longest_chain():

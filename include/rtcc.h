@@ -442,8 +442,9 @@ RTCC_API rtcc_status rtcc_node_count(rtcc_ctx *ctx, int32_t *n);
  * agent's map (a batched launch over several agents may use a wider tiling
  * of the same accumulation order: 1 or 9 for 2, 3 or 11 for 3 and 4, 10
  * for 8); plan[1] = K slices (1 = unsplit; where a plan splits tilings 2
- * and 4, the slices run side by side in one block, on any number of output
- * channels, and are added in slice order).  plan: caller-owned int32_t[2].  Errors: RTCC_E_ARG (NULL or layer out of
+ * and 4 at pixels of 128, 256 or 512 bytes, the slices run side by side in one
+ * block, on any number of output channels, or, over many maps, one after the
+ * other in the tilings named, and are added in slice order).  plan: caller-owned int32_t[2].  Errors: RTCC_E_ARG (NULL or layer out of
  * range), RTCC_E_STATE (the host test library has no kernels). */
 RTCC_API rtcc_status rtcc_conv_plan(rtcc_ctx *ctx, int32_t layer, int32_t *plan);
 

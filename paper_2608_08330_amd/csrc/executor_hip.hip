@@ -895,7 +895,12 @@ class HipExecutor : public Executor {
             hipEvent_t k0 = timing ? lead.kev[2 * l] : nullptr, k1 = timing ? lead.kev[2 * l + 1] : nullptr;
             ga.wfrag = d_frag_[l];
             ga.n_cu = n_cu_;
-            HIP_TRY(plans_[l].slices ? kern::conv_slices(p.bf16, ga, s, k0, k1) : kern::conv3x3(p.bf16, ga, s, k0, k1));
+            const bool side_by_side = plans_[l].slices && m < plans_[l].halo_maps;
+            if (plans_[l].slices && !side_by_side) {
+                ga.slices = ga.splits;
+                ga.splits = 1;
+            }
+            HIP_TRY(side_by_side ? kern::conv_slices(p.bf16, ga, s, k0, k1) : kern::conv3x3(p.bf16, ga, s, k0, k1));
             if (timing) HIP_TRY(hipEventRecord(lead.ev[ev], s));
             ++ev;
         }

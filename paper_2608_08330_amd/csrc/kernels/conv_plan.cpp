@@ -13,25 +13,51 @@ ConvPlan conv_plan(bool bf16, int Hi, int Wi, int Ci, int Ho, int Wo, int Co, in
     ConvPlan p{kConvImplicit, 1, 0, kConvImplicit, 1, kConvImplicit, 1 << 30, false};
     const int elt = bf16 ? 2 : 4;
     // Layers whose tiles do not fill the chip: the K slices of a tile summed
-    // side by side in one block (conv_slices.hip has the times).  The line is
-    // where a map's 4 x 16 x 128 tiles cover half the CUs: below it the halo
-    // tiling would be split over blocks (one map of 25 x 88 x 128 -> 128 9.8
-    // against 4.8 us); above it one map gains little or nothing (100 x 140 x
-    // 128 10.7 against 10.4, 80 x 100 x 256 19.8 against 20.5) and a batch
-    // loses (four maps of 100 x 140 x 128 23.5 against 28.8).  Without a
-    // 128-channel tiling, and for the 64-channel stride-2 entries below the
-    // 256-pixel implicit GEMM's line, the alternative is the split implicit
-    // GEMM, which is slower at every size (eight maps of 128 x 180 x 64 -> 64
-    // 64 against 24 us, five of 320 x 400 x 64 -> 128 stride 2 103 against 51).
+    // side by side in one block (conv_slices.hip has the times).
+    //
+    // With 128 k output channels the line is where a map's 4 x 16 x 128 tiles
+    // cover half the CUs: below it the halo tiling would be split over blocks, or
+    // leave the chip idle (one map of 25 x 88 x 128 -> 128 9.8 against 4.8 us);
+    // above it one map gains little or nothing (100 x 140 x 128 10.7 against
+    // 10.4, 80 x 100 x 256 19.8 against 20.5).  The 64-channel stride-2 entries
+    // take it up to the 256-pixel implicit GEMM's line (five maps of 320 x 400 x
+    // 64 -> 128 103 against 51; split implicit GEMM).
+    //
+    // Many maps fill the chip: a block of conv_slices reads its weights for 32 or
+    // 64 pixels only, so from 128 input channels with stride 2, and from 256 with
+    // stride 1, a launch takes the halo tilings from halo_maps maps on, which then
+    // sum the same slices (3 to 6% slower than without, from the extra sums).  The
+    // lines, in 4 x 16 x 128 tiles over all maps, are half the CUs for 512-byte
+    // pixels with stride 2, three quarters for 256-byte ones, all for stride 1.
+    // us, slices -> halo tilings, over the maps:
+    //   50 x 88 x 256 -> 25 x 44 x 256   3: 18.1 -> 19.6   4: 25.3 -> 20.2   8: 40.8 -> 30.2 (without slices 30.1)
+    //   128 x 128 x 128 -> 64 x 64 x 128 2: 10.1 -> 13.0   3: 14.3 -> 13.8   8: 28.5 -> 20.8 (20.0)
+    //   60 x 64 x 256 -> 256             1: 11.9 -> 17.9   2: 20.7 -> 19.4   8: 61.9 -> 43.7 (split-K 58.3)
+    // (eight maps of 128 x 180 x 64 -> 64 or 30 x 44 x 128 -> 128 stay with
+    // conv_slices: 24 and 10.8 against 64 and 25.6 as split-K.)
+    //
+    // Without a 128-channel tiling the alternative is the split implicit GEMM.
     const int slices = conv_slices_of(Ci * elt);
     if (slices) {
         const int t4 = ((Wo + 15) / 16) * ((Ho + 3) / 4) * (Co / 128);
-        const bool implicit256 = ((Ho * Wo + 255) / 256) * (Co / 128) >= n_cu;
-        const bool narrow = stride == 2 && Ci * elt < 256;
-        if (Co % 128 != 0 || t4 < n_cu / 2 || (narrow && !implicit256)) {
+        bool wins;
+        if (Co % 128 == 0) {
+            const bool implicit256 = ((Ho * Wo + 255) / 256) * (Co / 128) >= n_cu;
+            wins = t4 < n_cu / 2 || (stride == 2 && slices == 2 && !implicit256);
+        } else {
+            wins = true;
+        }
+        if (wins) {
             p.variant = p.variant_wide = p.variant_wider = stride == 1 ? kConvHalo4 : kConvHalo4S2;
             p.splits = slices;
             p.slices = true;
+            if (Co % 128 == 0) {
+                const int t8 = ((Wo + 15) / 16) * ((Ho + 7) / 8) * (Co / 128);
+                p.variant_wide = p.variant_wider = stride == 1 ? kConvHalo8 : kConvHalo8S2;
+                p.wide_maps = (n_cu + t8 - 1) / t8;
+                if (Ci * elt == 512) p.halo_maps = stride == 1 ? (n_cu + t4 - 1) / t4 : n_cu / 2 / t4 + 1;
+                else if (Ci * elt == 256 && stride == 2) p.halo_maps = (n_cu * 3 / 4 + t4 - 1) / t4;
+            }
             return p;
         }
     }

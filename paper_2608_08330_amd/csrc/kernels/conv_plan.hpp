@@ -57,6 +57,9 @@ struct ConvPlan {
     // adds: the summation order of tiling `variant` with `splits` slices, for
     // every batch size.
     bool slices = false;
+    // ... and from halo_maps maps on a launch runs the halo tilings above, which
+    // then sum the slices in the same order (GemmArgs::slices).
+    int halo_maps = 1 << 30;
 };
 // K slices of conv_slices for an input pixel of `row_bytes` bytes; 0: it has
 // no tile for this width.  64-byte channel chunks, one per slice, two per slice

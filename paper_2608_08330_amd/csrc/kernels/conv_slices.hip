@@ -16,15 +16,18 @@
 //     from the [N][K] matrix takes four times as long, the quads of lanes
 //     reading different rows;
 //   * adds the slices' partial sums in LDS in slice order and stores the tile.
-// The summation order is that of the split-K halo tilings with the same
-// number of slices (chunks ascending, then taps, then the chunk's substeps;
-// slices added in order), and does not depend on the tile shape: every tile
-// below gives the same bits, so the launch picks one by the number of maps.
+// The summation order is that of the halo tilings of the layer, cut into the
+// same slices: at 128- and 256-byte pixels a slice is one chunk, its taps
+// ascending; at 512 bytes it is two, with stride 1 tap by tap (one 128-byte
+// chunk of those tilings), with stride 2 one after the other; the slices are
+// added in order.  It does not depend on the tile shape: every tile below, and
+// the halo tilings with GemmArgs::slices, give the same bits, so the launch picks
+// one by the number of maps.
 //
 // Measured (us per launch; before: split-K tiles + k_splitk_reduce):
-//   one map    50 x 176 x 64 -> 64     12.4 -> 4.2   25 x 88 x 128 -> 128  9.8 -> 4.6
-//              13 x 44 x 256 -> 256     9.8 -> 5.1   64 x 64 x 32 -> 32 float32 13.5 -> 4.1
-//   three maps 128 x 128 x 64 -> 64    26.3 -> 8.4   64 x 64 x 128 -> 128 19.2 -> 8.0
+//   one map    50 x 176 x 64 -> 64     12.4 -> 4.4   25 x 88 x 128 -> 128  9.8 -> 4.8
+//              13 x 44 x 256 -> 256     9.8 -> 5.4   64 x 64 x 32 -> 32 float32 13.5 -> 4.1
+//   three maps 128 x 128 x 64 -> 64    26.3 -> 8.0   64 x 64 x 128 -> 128 19.2 -> 7.9
 //              32 x 32 x 256 -> 256    17.7 -> 8.9   256 x 256 x 64 -> 64 stride 2  23.9 -> 10.5
 //   eight maps 128 x 180 x 64 -> 64    65.4 -> 24.6  64 x 90 x 128 -> 128 36.3 -> 24.6
 #include "kernels.hpp"
@@ -122,19 +125,20 @@ __global__ __launch_bounds__(64 * S * WC) void k_conv_slices(GemmArgs a) {
 
     const int fr = lane & 15, fk = lane >> 4;
 #pragma unroll
-    for (int t = 0; t < 9; ++t) {
+    for (int q = 0; q < 9 * KS; ++q) {
+        // the halo tilings' order: at 512-byte rows with stride 1 both chunks of
+        // a slice tap by tap (a 128-byte chunk there), with stride 2 one after
+        // the other
+        const int t = STRIDE == 1 ? q / KS : q % 9, ks = STRIDE == 1 ? q % KS : q / 9;
         const int dy = t / 3, dx = t % 3;
+        const unsigned char *pa = smem + (slice * KS + ks) * (IA * 1024);
 #pragma unroll
-        for (int ks = 0; ks < KS; ++ks) {
-            const unsigned char *pa = smem + (slice * KS + ks) * (IA * 1024);
+        for (int i = 0; i < TH; ++i) {
+            const int col = STRIDE == 1 ? dx + fr : ((dx & 1) ? EVEN : dx >> 1) + fr;
+            const int r = (STRIDE * i + dy) * HW + col;
+            const uint4 x = *reinterpret_cast<const uint4 *>(pa + r * 64 + ((fk ^ ((r >> 1) & 3)) << 4));
 #pragma unroll
-            for (int i = 0; i < TH; ++i) {
-                const int col = STRIDE == 1 ? dx + fr : ((dx & 1) ? EVEN : dx >> 1) + fr;
-                const int r = (STRIDE * i + dy) * HW + col;
-                const uint4 x = *reinterpret_cast<const uint4 *>(pa + r * 64 + ((fk ^ ((r >> 1) & 3)) << 4));
-#pragma unroll
-                for (int j = 0; j < FN; ++j) acc[i][j] = Step<T>::mma(w[t * KS + ks][j], x, acc[i][j]);
-            }
+            for (int j = 0; j < FN; ++j) acc[i][j] = Step<T>::mma(w[t * KS + ks][j], x, acc[i][j]);
         }
     }
     __syncthreads();  // the patch is read; its LDS holds the partial tiles now

@@ -150,7 +150,8 @@ __device__ inline void store16_nt(void *p, uint4 v) {
 // gives the global element offset of tile pixel p's channel n0, or -1 to
 // skip it.  Called by every thread of the block (it holds two barriers);
 // `holds` is false for threads that hold no accumulators.
-template <typename T, int NPIX, int BN, int NT, int FM, int FN, typename PixF, typename RowF, typename ChF>
+template <typename T, int NPIX, int BN, int NT, int FM, int FN, bool STREAM = true, typename PixF, typename RowF,
+          typename ChF>
 __device__ inline void staged_store(unsigned char *stage, const f32x4_t (&acc)[FM][FN], bool holds, const float *bias,
                                     int n0, T *out, PixF pix, RowF row_of, ChF ch_of, int tid) {
     constexpr int RS = BN * int(sizeof(T)) + 16;
@@ -178,8 +179,10 @@ __device__ inline void staged_store(unsigned char *stage, const f32x4_t (&acc)[F
         const int p = v / VPP, part = v - (v / VPP) * VPP;
         const int64_t off = pix(p);
         if (off < 0) continue;
-        store16_nt(reinterpret_cast<uint4 *>(out + off) + part,
-                   *reinterpret_cast<const uint4 *>(stage + p * RS + part * 16));
+        uint4 *dst = reinterpret_cast<uint4 *>(out + off) + part;
+        const uint4 x = *reinterpret_cast<const uint4 *>(stage + p * RS + part * 16);
+        if (STREAM) store16_nt(dst, x);
+        else *dst = x;
     }
 }
 
@@ -448,7 +451,10 @@ __global__ __launch_bounds__(64 * WGM * WGN) void k_igemm(GemmArgs a0) {
 // once step s's weights have landed, the loads still allowed in flight are
 // the weights of the next R - 2 steps plus, at taps 1 .. R - 1, the next
 // chunk's patch (issued at tap 0 after the weights of step s + R - 1).
-template <typename T, int TH, int BN, int WGM, int WGN, int RB, int STRIDE, int KG, int R, bool ILV>
+// With SL the channel chunks are summed in a.slices slices of their own, added
+// in slice order: the order of conv_slices, for the launches of a plan that
+// takes it over many maps.
+template <typename T, int TH, int BN, int WGM, int WGN, int RB, int STRIDE, int KG, int R, bool ILV, bool SL>
 __global__ __launch_bounds__(64 * WGM * WGN * KG) void k_conv3s1(GemmArgs a0) {
     constexpr int NW = WGM * WGN;  // wavefronts per group
     constexpr int EPV = Traits<T>::EPV;
@@ -656,8 +662,36 @@ __global__ __launch_bounds__(64 * WGM * WGN * KG) void k_conv3s1(GemmArgs a0) {
         step(std::integral_constant<int, 7>{}, lastc, c);
         step(std::integral_constant<int, 8>{}, lastc, c);
     };
-    for (int c = 0; c + 1 < CH; ++c) chunk(std::false_type{}, c);
+    f32x4_t sum[SL ? FM : 1][SL ? FN : 1];  // the slices before
+    const int per_slice = SL ? CH / a.slices : 1;
+    int done = 0, in_slice = 0;
+    // after a chunk that is not the last
+    auto end_slice = [&]() {
+        if (++in_slice < per_slice) return;
+        in_slice = 0;
+#pragma unroll
+        for (int i = 0; i < FM; ++i)
+#pragma unroll
+            for (int j = 0; j < FN; ++j) {
+                if (done == 0) sum[i][j] = acc[i][j];
+                else sum[i][j] += acc[i][j];
+                acc[i][j] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+            }
+        ++done;
+    };
+    for (int c = 0; c + 1 < CH; ++c) {
+        chunk(std::false_type{}, c);
+        if constexpr (SL) end_slice();
+    }
     chunk(std::true_type{}, CH - 1);
+    if constexpr (SL) {
+        if (done > 0) {
+#pragma unroll
+            for (int i = 0; i < FM; ++i)
+#pragma unroll
+                for (int j = 0; j < FN; ++j) acc[i][j] = sum[i][j] + acc[i][j];
+        }
+    }
 
     if constexpr (KG > 1) {
         // every wave has read its last LDS operands and every DMA load has
@@ -694,7 +728,8 @@ __global__ __launch_bounds__(64 * WGM * WGN * KG) void k_conv3s1(GemmArgs a0) {
         if (a.splits == 1) {
             // the staging tile overwrites the reduction area: staged_store
             // starts with a barrier, after group 0 has read it
-            staged_store<T, TH * TW, BN, 64 * NW * KG, FM, FN>(
+            // (the small maps of the plans with slices stay in the L2)
+            staged_store<T, TH * TW, BN, 64 * NW * KG, FM, FN, !SL>(
                 smem, acc, grp == 0, a.bias, n0, static_cast<T *>(a.out),
                 [&](int p) -> int64_t {
                     const int oy = oy0 + p / TW, ox = ox0 + p % TW;
@@ -777,12 +812,12 @@ hipError_t launch_cfg(const GemmArgs &a, hipStream_t s, hipEvent_t e0 = nullptr,
     return launch_kernel(k_splitk_reduce<T>, dim3(unsigned((total + 255) / 256), nb), dim3(256), s, nullptr, e1, a);
 }
 
-template <typename T, int TH, int BN, int WGM, int WGN, int RB, int STRIDE, int KG, int R, bool ILV>
+template <typename T, int TH, int BN, int WGM, int WGN, int RB, int STRIDE, int KG, int R, bool ILV, bool SL = false>
 hipError_t launch_halo(const GemmArgs &a, hipStream_t s, hipEvent_t e0 = nullptr, hipEvent_t e1 = nullptr) {
     const unsigned nb = unsigned(a.batch > 1 ? a.batch : 1);
     const unsigned tiles = unsigned((a.Wo + 15) / 16) * unsigned((a.Ho + TH - 1) / TH);
     const unsigned nx = tiles * unsigned(a.N / BN) * unsigned(a.splits) * nb;
-    hipError_t e = launch_kernel(k_conv3s1<T, TH, BN, WGM, WGN, RB, STRIDE, KG, R, ILV>, dim3(nx),
+    hipError_t e = launch_kernel(k_conv3s1<T, TH, BN, WGM, WGN, RB, STRIDE, KG, R, ILV, SL>, dim3(nx),
                                  dim3(64 * WGM * WGN * KG), s, e0, a.splits == 1 ? e1 : nullptr, a);
     if (e != hipSuccess || a.splits == 1) return e;
     const int64_t total = int64_t(a.Ho) * a.Wo * (a.N / 4);
@@ -795,6 +830,21 @@ hipError_t launch(const GemmArgs &a, hipStream_t s, hipEvent_t e0 = nullptr, hip
         // 128-byte K steps pay off from 256 input channels (bf16) on, where
         // one block holds a CU (kConvHalo8C64 keeps 64-byte steps)
         const bool rb128 = (a.Ci * int(sizeof(T))) % 128 == 0 && a.Ci * int(sizeof(T)) >= 512;
+        if (a.slices > 1) {  // the plans of conv_slices, over many maps
+            const int chunks = a.Ci * int(sizeof(T)) / (rb128 && a.stride == 1 ? 128 : 64);
+            if (a.splits != 1 || chunks % a.slices != 0) return hipErrorInvalidValue;
+            switch (a.variant) {
+                case kConvHalo8:
+                    return rb128 ? launch_halo<T, 8, 128, 4, 2, 128, 1, 1, 4, true, true>(a, s, e0, e1)
+                                 : launch_halo<T, 8, 128, 4, 2, 64, 1, 1, 4, false, true>(a, s, e0, e1);
+                case kConvHalo4:
+                    return rb128 ? launch_halo<T, 4, 128, 2, 2, 128, 1, 1, 3, true, true>(a, s, e0, e1)
+                                 : launch_halo<T, 4, 128, 2, 2, 64, 1, 1, 3, true, true>(a, s, e0, e1);
+                case kConvHalo8S2: return launch_halo<T, 8, 128, 4, 2, 64, 2, 1, 4, true, true>(a, s, e0, e1);
+                case kConvHalo4S2: return launch_halo<T, 4, 128, 4, 2, 64, 2, 1, 4, true, true>(a, s, e0, e1);
+                default: return hipErrorInvalidValue;
+            }
+        }
         // template arguments: TH, BN, WGM, WGN, RB, STRIDE, KG, weight ring
         // depth R, interleaved LDS reads; R and the interleaving as they
         // measured fastest at the c5 shapes

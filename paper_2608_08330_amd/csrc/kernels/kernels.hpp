@@ -159,6 +159,7 @@ struct GemmArgs {
     float *ws_b[16];
     const void *wfrag; // conv_slices: the weights in fragment order (conv_frag)
     int32_t n_cu;      // conv_slices: compute units of the GPU
+    int32_t slices;    // halo tilings, > 1: the channel chunks in that many slices, added in order (splits = 1)
 };
 // With start / stop events, the first kernel of the convolution records
 // `start` when it begins executing and the last one `stop` when it ends
@@ -166,9 +167,9 @@ struct GemmArgs {
 hipError_t conv3x3(bool bf16, const GemmArgs &a, hipStream_t s, hipEvent_t start = nullptr,
                    hipEvent_t stop = nullptr);
 hipError_t deconv(bool bf16, const GemmArgs &a, hipStream_t s);
-// The convolution of a plan with ConvPlan::slices: the K slices of a tile side
-// by side in one block, summed there (no ws).  Needs wfrag and n_cu, and
-// splits = conv_slices_of(Ci * element size).
+// The convolution of a plan with ConvPlan::slices, below its halo_maps: the K
+// slices of a tile side by side in one block, summed there (no ws).  Needs
+// wfrag and n_cu, and splits = conv_slices_of(Ci * element size).
 hipError_t conv_slices(bool bf16, const GemmArgs &a, hipStream_t s, hipEvent_t start = nullptr,
                        hipEvent_t stop = nullptr);
 // Bt [N][9 Ci] (N a multiple of 16) to the order conv_slices reads; as large.

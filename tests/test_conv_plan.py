@@ -4,7 +4,12 @@ layer shape of the configs, for several CU counts and every batch size, the
 invariant that lets a group release equal separate releases bit for bit:
 all tilings a layer takes accumulate each output element in the same order
 (the same channel chunks and taps, so the same chunk width and one wave
-group), with the same K split."""
+group), with the same K split.  Where the K slices of a tile are summed side by
+side in one block, and from how many maps on by the halo tilings, is not part of
+the C ABI: the planner is compiled into a small program of its own."""
+
+import os
+import subprocess
 
 import pytest
 
@@ -80,6 +85,62 @@ def test_every_batch_size_accumulates_alike(name, n_cu):
                 assert v not in HALO_S2
             elif v not in IMPLICIT + IMPLICIT256:
                 assert v in HALO_S2
+
+
+PROGRAM = r"""
+#include <cstdio>
+#include "conv_plan.hpp"
+using namespace rtcc::kern;
+int main() {
+    int b, s[8];
+    while (std::scanf("%d %d %d %d %d %d %d %d %d", &b, s, s + 1, s + 2, s + 3, s + 4, s + 5, s + 6, s + 7) == 9) {
+        const ConvPlan p = conv_plan(b != 0, s[0], s[1], s[2], s[3], s[4], s[5], s[6], s[7]);
+        std::printf("%d %d %d %zu\n", int(p.slices), p.splits, p.halo_maps, p.ws_bytes);
+    }
+}
+"""
+
+
+@pytest.fixture(scope="module")
+def planner(tmp_path_factory):
+    d = tmp_path_factory.mktemp("planner")
+    src = os.path.join(os.path.dirname(R.__file__), "csrc", "kernels")
+    (d / "main.cpp").write_text(PROGRAM)
+    subprocess.run(["g++", "-std=c++17", "-I" + src, str(d / "main.cpp"), os.path.join(src, "conv_plan.cpp"),
+                    "-o", str(d / "planner")], check=True)
+
+    def plan(bf16, Ci, Ho, Wo, Co, stride, n_cu=256):
+        """(slices side by side or 0, maps from which the halo tilings sum them or None)"""
+        shape = (int(bf16), Ho * stride, Wo * stride, Ci, Ho, Wo, Co, stride, n_cu)
+        r = subprocess.run([str(d / "planner")], input=" ".join(map(str, shape)), text=True, check=True,
+                           stdout=subprocess.PIPE).stdout.split()
+        if not int(r[0]):
+            return 0, None
+        assert int(r[3]) == 0  # no partial sums in memory
+        return int(r[1]), int(r[2]) if int(r[2]) < 1 << 30 else None
+    return plan
+
+
+@pytest.mark.parametrize("shape,want", [
+    # widths: pixels of 128, 256 and 512 bytes
+    ((True, 32, 20, 20, 128, 1), (0, None)), ((True, 64, 20, 20, 128, 1), (2, None)),
+    ((True, 96, 20, 20, 128, 1), (0, None)), ((True, 128, 20, 20, 128, 1), (4, None)),
+    ((True, 256, 20, 20, 128, 1), (4, 26)), ((True, 512, 20, 20, 128, 1), (0, None)),
+    ((False, 32, 20, 20, 128, 1), (2, None)), ((False, 64, 20, 20, 128, 1), (4, None)),
+    ((False, 128, 20, 20, 128, 1), (4, 26)),
+    # 128 k output channels: up to half the CUs in 4 x 16 x 128 tiles
+    ((True, 128, 508, 16, 128, 1), (4, None)), ((True, 128, 509, 16, 128, 1), (0, None)),
+    ((True, 128, 252, 16, 256, 2), (4, 2)), ((True, 128, 253, 16, 256, 2), (0, None)),
+    ((True, 128, 252, 16, 256, 2, 128), (0, None)),
+    # ... and the 64-channel entries up to the 256-pixel implicit GEMM's line
+    ((True, 64, 255, 256, 128, 2), (2, None)), ((True, 64, 256, 256, 128, 2), (0, None)),
+    ((True, 64, 256, 256, 128, 1), (0, None)),
+    # the maps from which the halo tilings run: 256 tiles, 129, 192
+    ((True, 256, 64, 64, 128, 1), (4, 4)), ((True, 256, 64, 60, 128, 2), (4, 3)), ((True, 256, 60, 64, 128, 2), (4, 3)),
+    ((True, 128, 64, 64, 128, 2), (4, 3)), ((True, 128, 60, 64, 128, 2), (4, 4)), ((True, 128, 64, 64, 128, 1), (4, None)),
+])
+def test_where_slices_are_summed_side_by_side(planner, shape, want):
+    assert planner(*shape) == want
 
 
 def test_arguments_are_checked():

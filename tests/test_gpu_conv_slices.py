@@ -1,10 +1,11 @@
 """The 3x3 convolutions whose K slices run side by side in one block: every
 channel width (two slices, four, four of two chunks), both strides, float32
 and bf16, on grids with ragged tiles, one map per launch (two-row tiles) and
-eight maps per launch (the larger tiles).  Every layer elementwise against the
-oracle convolution of its GPU input, and the group launch bit for bit equal to
-separate launches (the tiles sum in the same order).  The upsamplings of the
-same networks (one launch for all stages, or one each) likewise."""
+eight maps per launch (the larger tiles, and the halo tilings that sum the
+same slices).  Every layer elementwise against the oracle convolution of its
+GPU input, and the group launch bit for bit equal to separate launches (the
+tiles sum in the same order).  The upsamplings of the same networks (one launch
+for all stages, or one each) likewise."""
 
 import copy
 
@@ -30,6 +31,12 @@ SHAPES = [
     # eight maps: more blocks than the one-group upsampling takes, 64 / 128 / 256 input channels
     ("many_up", "bf16", 64, ((1, 64, 1), (2, 128, 1), (2, 256, 1)), 128, (197, 203)),
     ("fp32", "fp32", 64, ((2, 32, 2),), 32, (47, 95)),
+    # group launches by the halo tilings: 8 rows of 16 pixels, strides 1 and 2 ...
+    ("halo", "bf16", 128, ((2, 256, 2), (2, 256, 1)), 128, (90, 100)),
+    ("fp32_128", "fp32", 128, ((1, 128, 1), (2, 128, 1)), 64, (47, 95)),
+    ("fp32_64", "fp32", 64, ((1, 64, 1), (2, 128, 1)), 64, (130, 131)),
+    # ... 4 rows
+    ("halo4", "bf16", 256, ((1, 128, 1),), 0, (40, 60)),
 ]
 
 
@@ -76,7 +83,15 @@ def test_slices_against_the_oracle_and_between_batch_sizes(name, precision, c_pf
     n_layers = sum(n for _s, _c, n in stages)
     with make_ctx(cfg, fr) as ctx:
         plans = [R.rtcc_conv_plan(ctx, l) for l in range(n_layers)]
-        assert any(v in (2, 4) and s in (2, 4) for v, s in plans), plans
+        # every layer of these shapes but those of 96 input channels, whose
+        # pixels are no 128, 256 or 512 bytes (test_conv_plan.py has the rule)
+        ci, l = c_pfn, 0
+        for stride, co, n in stages:
+            for s in (stride,) + (1,) * (n - 1):
+                slices = {128: 2, 256: 4, 512: 4}.get(ci * (2 if precision == "bf16" else 4))
+                if slices:
+                    assert tuple(plans[l]) == (2 if s == 1 else 4, slices), (l, plans)
+                ci, l = co, l + 1
         got = []
         for group in (False, True):
             _run(ctx, fr, group)

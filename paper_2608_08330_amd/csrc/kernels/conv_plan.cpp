@@ -36,7 +36,19 @@ ConvPlan conv_plan(bool bf16, int Hi, int Wi, int Ci, int Ho, int Wo, int Co, in
     // (eight maps of 128 x 180 x 64 -> 64 or 30 x 44 x 128 -> 128 stay with
     // conv_slices: 24 and 10.8 against 64 and 25.6 as split-K.)
     //
-    // Without a 128-channel tiling the alternative is the split implicit GEMM.
+    // Without a 128-channel tiling the alternative is the implicit GEMM, split
+    // over K below one tile per CU.  It is slower with stride 1 and for 64 input
+    // channels (100 x 352 to 512 x 512 cells, 32 to 192 output channels, one map
+    // and eight).  With stride 2 the slices' patch is twice as large; us, GEMM
+    // against slices, one map and eight:
+    //   128 -> 192  128 x 128 30.6 : 22.1, 137 : 137   180 x 180 42.0 : 41.8, 274 : 303
+    //   128 -> 96   128 x 128 25.8 : 15.1, 94 : 86     256 x 256 55.8 : 45.6, 394 : 327
+    //   256 -> 32   128 x 128 22.8 : 14.7, 118 : 80    256 x 256 54 : 42, 369 : 334
+    //   256 -> 96   50 x 176  29.6 : 21.9, 130 : 130   90 x 90 24.9 : 21.9, 119 : 123   128 x 128 45 : 32, 183 : 221
+    //   256 -> 192  50 x 176  35.8 : 34.6, 191 : 188   128 x 128 53.8 : 48.5, 265 : 363
+    // so from 128 channels they take the widths that leave the GEMM's last 64
+    // channels half empty, and others below two tiles per CU; from 256 channels
+    // 32 outputs, and others below five tiles per eight CUs.
     const int slices = conv_slices_of(Ci * elt);
     if (slices) {
         const int t4 = ((Wo + 15) / 16) * ((Ho + 3) / 4) * (Co / 128);
@@ -45,7 +57,9 @@ ConvPlan conv_plan(bool bf16, int Hi, int Wi, int Ci, int Ho, int Wo, int Co, in
             const bool implicit256 = ((Ho * Wo + 255) / 256) * (Co / 128) >= n_cu;
             wins = t4 < n_cu / 2 || (stride == 2 && slices == 2 && !implicit256);
         } else {
-            wins = true;
+            const int tiles = gemm_tiles(Ho * Wo, Co);
+            wins = stride == 1 || slices == 2 || Co <= 32 ||
+                   (Ci * elt == 256 ? Co % 64 != 0 || tiles < 2 * n_cu : tiles < n_cu * 5 / 8);
         }
         if (wins) {
             p.variant = p.variant_wide = p.variant_wider = stride == 1 ? kConvHalo4 : kConvHalo4S2;

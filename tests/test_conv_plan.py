@@ -135,6 +135,14 @@ def planner(tmp_path_factory):
     # ... and the 64-channel entries up to the 256-pixel implicit GEMM's line
     ((True, 64, 255, 256, 128, 2), (2, None)), ((True, 64, 256, 256, 128, 2), (0, None)),
     ((True, 64, 256, 256, 128, 1), (0, None)),
+    # other output channels: always with stride 1 or 64 input channels
+    ((True, 256, 2000, 2000, 96, 1), (4, None)), ((True, 64, 2000, 2000, 192, 2), (2, None)),
+    # stride 2 from 128 channels: where the GEMM's last 64 channels are not all used, or below two tiles per CU
+    ((True, 128, 2000, 2000, 96, 2), (4, None)), ((True, 128, 170, 128, 192, 2), (4, None)),
+    ((True, 128, 171, 128, 192, 2), (0, None)), ((False, 64, 171, 128, 192, 2), (0, None)),
+    # from 256: up to 32 channels, or below 5 tiles per 8 CUs
+    ((True, 256, 2000, 2000, 32, 2), (4, None)), ((True, 256, 79, 128, 96, 2), (4, None)),
+    ((True, 256, 80, 128, 96, 2), (0, None)), ((True, 256, 80, 128, 64, 2), (4, None)),
     # the maps from which the halo tilings run: 256 tiles, 129, 192
     ((True, 256, 64, 64, 128, 1), (4, 4)), ((True, 256, 64, 60, 128, 2), (4, 3)), ((True, 256, 60, 64, 128, 2), (4, 3)),
     ((True, 128, 64, 64, 128, 2), (4, 3)), ((True, 128, 60, 64, 128, 2), (4, 4)), ((True, 128, 64, 64, 128, 1), (4, None)),

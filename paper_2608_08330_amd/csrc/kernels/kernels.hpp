@@ -182,7 +182,7 @@ struct UpsampleStage {
     const float *bias;   // [Co]
     int32_t Hi, Wi, Ci;  // input map
     int32_t u, c_off;    // kernel = stride; first output channel in the slot
-    int32_t per, blocks; // set by upsample
+    int32_t per, blocks, run; // set by upsample: groups per block, blocks per map, blocks per XCD
 };
 struct UpsampleArgs {
     UpsampleStage stage[4];

@@ -179,16 +179,19 @@ __device__ inline void up_tile(const UpsampleArgs &a, const UpsampleStage &st, c
 template <int P>
 __global__ __launch_bounds__(256 / P, 2) void k_upsample(UpsampleArgs a) {
     __shared__ __attribute__((aligned(1024))) unsigned char smem[kPx * 256 * 2];
-    // each XCD takes a contiguous run of blocks; map bt's blocks are one run
-    int bid = blockIdx.x;
-    const int nbx = gridDim.x;
-    if ((nbx & 7) == 0) bid = (bid & 7) * (nbx >> 3) + (bid >> 3);
-    const int per_map = nbx / a.batch;
-    const int bt = bid / per_map;
-    bid -= bt * per_map;
-    int s = 0;
-    while (bid >= a.stage[s].blocks) bid -= a.stage[s++].blocks;
+    // each XCD takes a contiguous run of every stage's blocks (a stage's blocks
+    // are one run per map): a stage with many channels costs several times as
+    // much per block, and as one run over all stages its blocks had a few XCDs to
+    // themselves (64 / 128 / 256 channels at 256 x 256: one map 49 -> 39 us, three
+    // 103 -> 82, eight, a map per XCD either way, 154)
+    const int xcd = blockIdx.x & 7;
+    int b = blockIdx.x >> 3, s = 0;
+    while (b >= a.stage[s].run) b -= a.stage[s++].run;
     const UpsampleStage &st = a.stage[s];
+    b += xcd * st.run;
+    const int bt = b / st.blocks;
+    if (bt >= a.batch) return;
+    const int bid = b - bt * st.blocks;
     const int groups = st.u * st.u * (a.Co >> 7);
     const int runs = (groups + st.per - 1) / st.per;  // blocks per 64 pixels
     const int m0 = bid / runs * kPx, g0 = bid % runs * st.per;
@@ -244,10 +247,11 @@ hipError_t upsample(UpsampleArgs a, hipStream_t s) {
         const int groups = st.u * st.u * (a.Co >> 7);
         st.per = per < groups ? per : groups;
         st.blocks = (st.Hi * st.Wi + kPx - 1) / kPx * ((groups + st.per - 1) / st.per);
-        blocks += st.blocks;
+        st.run = int32_t((int64_t(st.blocks) * a.batch + 7) / 8);
+        blocks += int64_t(st.run) * 8;
     }
-    if (many) k_upsample<2><<<unsigned(blocks * a.batch), 128, 0, s>>>(a);
-    else k_upsample<1><<<unsigned(blocks * a.batch), 256, 0, s>>>(a);
+    if (many) k_upsample<2><<<unsigned(blocks), 128, 0, s>>>(a);
+    else k_upsample<1><<<unsigned(blocks), 256, 0, s>>>(a);
     return hipGetLastError();
 }
 

@@ -227,30 +227,43 @@ hipError_t upsample_frag(const void *wt, void *out, int32_t u, int32_t Co, int32
 }
 
 hipError_t upsample(UpsampleArgs a, hipStream_t s) {
-    // One group per block and P = 1, for the shortest chain, until the blocks
-    // are many times what runs at once; then four groups, so that the pixels
-    // are staged for four phases, and P = 2.  us, one group and P = 1 -> four
-    // and P = 2, over the blocks of the former: 3,072 (one 256 x 256 map)
-    // 24 -> 44, 12,288 (four) 97 -> 106, 16,896 113 -> 98, 18,432 (six) 136 ->
-    // 125, 24,576 (eight) 173 -> 153
+    // One group per block and P = 1, for the shortest chain, while the blocks are
+    // not many times what runs at once; from there on P = 2 and more groups per
+    // block, whose pixels are staged once for all of them: every group of the
+    // pixel at u = 1, two of a larger kernel's, and four once the blocks are many
+    // more.  A single group per pixel (one stage, u = 1, 128 channels) has
+    // nothing to share.  And P = 2 where its blocks, four per CU, run all at once
+    // and those of P = 1, three per CU, do not.  us, over the blocks of one group,
+    // P = 1 -> P = 2 (groups per block):
+    //   one stage, 256 -> 128    825  17.3 -> 15.3 (1)    1,024 20.1 -> 17.3 (1)    2,048 32.4 -> 34.8 (1)
+    //   one stage, 256 -> 256  4,096  50.1 -> 45.5 (2)    6,144 65.5 -> 62.2 (2)
+    //   one stage, 256 -> 384    768  12.9 -> 16.2 (2)    3,072 39.6 -> 28.4 (3)    6,144 69.9 -> 60.5 (3)
+    //   64 / 128 / 256 -> 128  1,768  27.9 -> 29.4 (2)    3,072 39.4 -> 37.0 (2)    9,216 81.6 -> 73.0 (2)
+    //                         24,576 189.5 -> 158.3 (2), 153.0 (4)
+    //   64 / 128 -> 256        2,256  23.5 -> 23.1 (2)    8,192 52.8 -> 47.2 (2)    12,288 74.3 -> 61.0 (2)
     int64_t single = 0;
+    bool shared = false;
     for (int q = 0; q < a.n_stages; ++q) {
         const UpsampleStage &st = a.stage[q];
         if (!upsample_fits(true, st.Ci, a.Co)) return hipErrorInvalidValue;
-        single += int64_t((st.Hi * st.Wi + kPx - 1) / kPx) * st.u * st.u * (a.Co >> 7);
+        const int groups = st.u * st.u * (a.Co >> 7);
+        single += int64_t((st.Hi * st.Wi + kPx - 1) / kPx) * groups;
+        shared = shared || groups > 1;
     }
-    const bool many = single * a.batch > 14336;
-    const int per = many ? 4 : 1;
+    single *= a.batch;
+    const bool many = single > 14336, some = shared && single > 2560;
+    const bool two = many || some || (single > 768 && single <= 1024);
     int64_t blocks = 0;
     for (int q = 0; q < a.n_stages; ++q) {
         UpsampleStage &st = a.stage[q];
         const int groups = st.u * st.u * (a.Co >> 7);
+        const int per = many || (some && st.u == 1) ? 4 : some ? 2 : 1;
         st.per = per < groups ? per : groups;
         st.blocks = (st.Hi * st.Wi + kPx - 1) / kPx * ((groups + st.per - 1) / st.per);
         st.run = int32_t((int64_t(st.blocks) * a.batch + 7) / 8);
         blocks += int64_t(st.run) * 8;
     }
-    if (many) k_upsample<2><<<unsigned(blocks), 128, 0, s>>>(a);
+    if (two) k_upsample<2><<<unsigned(blocks), 128, 0, s>>>(a);
     else k_upsample<1><<<unsigned(blocks), 256, 0, s>>>(a);
     return hipGetLastError();
 }

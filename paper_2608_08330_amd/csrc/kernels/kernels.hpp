@@ -69,8 +69,14 @@ struct PointsUpload {
 };
 hipError_t points_upload(const PointsUpload &u, hipStream_t s);
 
-// Points from which on a pillar is crowded: above the cap, and above a few.
-inline int32_t pfn_crowd(int32_t max_pts) { return max_pts < 4 ? max_pts : 4; }
+// A pillar of more points is crowded: above the cap, or above a few, where a
+// lane's walk over the points costs more than a wavefront for the pillar.  Six,
+// so that a cloud spread over its cells evenly, three points in each, has few of
+// them (pfn_canvas, us, more than four / six / eight / twelve points):
+//   clustered  100,000 on 512 x 512 cells      13.6 / 12.1 / 12.7 / 13.4
+//              6,000 on 352 x 100               7.6 /  8.0 /  8.6 / 11.3
+//   even       100,000 on 352 x 100            16.6 / 10.9 / 11.3 / 11.7
+inline int32_t pfn_crowd(int32_t max_pts) { return max_pts < 6 ? max_pts : 6; }
 
 // The sort of points by cell (counting in LDS):
 // K1 bin_count: cell id per point (-1 if dropped); per block of

@@ -466,9 +466,7 @@ __device__ inline void store_canvas8(const PfnArgs &a, void *canvas, int cell, i
 // multiply-adds in a row.  Of a pillar over the cap that wavefront first moves
 // the cap lowest point indices to the front of its segment (member indices
 // and points).  The other cells of the canvas already hold zeros.  One agent with 40,000 points 16.6 -> 7.3 us, 6,000
-// on 2,640 cells 13.5 -> 5.1, 100,000 on 512 x 512 cells 12.8 -> 10.8 (eight of
-// these in a launch, where the wavefronts have others to hide behind, 38.6 ->
-// 41.8).
+// on 2,640 cells 13.5 -> 5.1, 100,000 on 512 x 512 cells 12.8 -> 10.8.
 template <bool BF16>
 __global__ __launch_bounds__(256) void k_pfn_canvas(const PfnArgs a, const PillarGroup grp) {
     // PFN weights and bias, read once per block into LDS (C <= 512)
@@ -682,9 +680,12 @@ hipError_t pillars_small(const PillarGroup &grp, const PillarGeom &g, int32_t cr
 
 hipError_t pfn_canvas(bool bf16, PfnArgs a, const PillarGroup &grp, int32_t max_pillars, hipStream_t s) {
     // blocks for the crowded pillars (four at a time each), which take the
-    // longest, then the others
-    const unsigned crowds = blocks_for(grp.n_max / (a.crowd + 1), 4);
-    a.crowd_blocks = int32_t(crowds < 256u ? crowds : 256u);
+    // longest, then the others.  At most one per CU over all agents: more hold the
+    // others up (eight agents with 100,000 points, 256 for each -> for all, us:
+    // clustered on 512 x 512 cells 43.8 -> 41.0, spread evenly 41.0 -> 39.2, on 352
+    // x 100 cells 32.3 -> 29.8; over the cap only 53, 39, 29.6)
+    const unsigned crowds = blocks_for(grp.n_max / (a.crowd + 1), 4), most = 256u / unsigned(grp.m);
+    a.crowd_blocks = int32_t(crowds < most ? crowds : most);
     const unsigned blocks = unsigned(a.crowd_blocks) + blocks_for(int64_t((max_pillars + 1) / 2) * (a.C / 8), 256);
     if (blocks == 0) return hipSuccess;
     const unsigned grid = blocks * unsigned(grp.m);

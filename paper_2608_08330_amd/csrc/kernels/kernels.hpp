@@ -105,8 +105,9 @@ hipError_t tile_sort(const PillarGroup &grp, int32_t crowd, hipStream_t s);
 //   352 x 100, four releases       4,000 413 -> 436, 8,000 422 -> 440;
 //     a group of eight             4,000 357 -> 356, 8,000 380 -> 366
 constexpr int kSmallPoints = 8192, kSmallCells = 16384;
-inline bool pillars_small_fits(int n_cells, int n_max) {
-    return n_cells <= kSmallCells ? n_max <= kSmallPoints : n_cells <= kSmallCells * 4 && n_max <= kSmallPoints / 2;
+inline bool pillars_small_fits(int n_cells, int n_max, bool host_bound) {
+    const int points = host_bound ? kSmallPoints : kSmallPoints / 2;
+    return n_cells <= kSmallCells ? n_max <= points : n_cells <= kSmallCells * 4 && n_max <= points / 2;
 }
 hipError_t pillars_small(const PillarGroup &grp, const PillarGeom &g, int32_t crowd, hipStream_t s);
 // K4 pfn_canvas: the dense canvas [H*W][C]: per pillar cell, channel max over the first

@@ -671,7 +671,7 @@ hipError_t tile_sort(const PillarGroup &grp, int32_t crowd, hipStream_t s) {
 }
 
 hipError_t pillars_small(const PillarGroup &grp, const PillarGeom &g, int32_t crowd, hipStream_t s) {
-    if (!pillars_small_fits(grp.n_cells, grp.n_max)) return hipErrorInvalidValue;
+    if (!pillars_small_fits(grp.n_cells, grp.n_max, true)) return hipErrorInvalidValue;
     const unsigned blocks = unsigned(grp.m);
     if (grp.n_cells <= kSmallCells) k_pillars_small<kSmallCells, kSmallPoints / 1024><<<blocks, 1024, 0, s>>>(grp, g, crowd);
     else k_pillars_small<kSmallCells * 4, kSmallPoints / 2048><<<blocks, 1024, 0, s>>>(grp, g, crowd);

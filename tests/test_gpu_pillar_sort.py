@@ -6,6 +6,7 @@ cells, where each of the two tiles holds far more points than the tile
 sort keeps in registers and every pillar is over the cap."""
 
 import sys
+import time
 
 import numpy as np
 import pytest
@@ -67,12 +68,13 @@ def test_fifteen_million_points_on_two_tiles():
 
 
 # (H, W) cells and points: one block per agent up to 8,192 points and 16,384
-# cells or 4,096 points and 65,536 cells, tiles of 512 cells up to 131,072 cells
-# and of 2,048 above
+# cells or 4,096 points and 65,536 cells (half the points for a group), tiles of
+# 512 cells up to 131,072 cells and of 2,048 above
 @pytest.mark.parametrize("grid,n", [
     ((1, 1), 40), ((3, 5), 0), ((3, 5), 1), ((128, 128), 1024), ((128, 129), 1025), ((127, 129), 16384),
     ((256, 256), 16384), ((256, 256), 16385), ((128, 128), 8192), ((128, 128), 8193),
     ((128, 129), 4096), ((128, 129), 4097), ((256, 256), 4096), ((256, 257), 4096),
+    ((128, 129), 2048), ((128, 129), 2049),
     ((256, 257), 1023), ((11, 5958), 5000), ((512, 1), 513),
     ((256, 512), 20000), ((257, 511), 20000), ((2, 70001), 30000),
 ])
@@ -96,8 +98,14 @@ def test_sizes_at_the_edges_of_the_paths(grid, n):
         clouds.append(p[rng.permutation(n)])
     fr = dict(points=clouds, poses=np.zeros((2, 3)), weights=synth.make_weights(synth.config("c1")))
     with make_ctx(cfg, fr, max_points=max(n, 1)) as ctx:
-        for points in (clouds, clouds[::-1]):
-            run_frame(ctx, fr, points=points)
+        for points, group in ((clouds, False), (clouds[::-1], False), (clouds, True)):
+            if group:
+                R.rtcc_begin_frame(ctx, time.monotonic() - 1.0)
+                R.rtcc_release_branches(ctx, [dict(agent=k, points=p, pose=fr["poses"][k], arrival_t=0.0)
+                                              for k, p in enumerate(points)])
+                R.rtcc_join_and_detect(ctx)
+            else:
+                run_frame(ctx, fr, points=points)
             for k in range(2):
                 _check_pillars(ctx, cfg, points[k], k)
                 canvas = R.rtcc_get_tensor(ctx, R.RTCC_T_CANVAS, k, np.float32).reshape(H * W, -1)

@@ -79,7 +79,8 @@ class HipExecutor : public Executor {
         br_.resize(p.K);
         for (int k = 0; k < p.K; ++k) {
             Branch &b = br_[k];
-            HIP_TRY(hipHostMalloc(reinterpret_cast<void **>(&b.staging), n_max * 16, hipHostMallocDefault));
+            // (coherent: refilled every frame and read by points_upload)
+            HIP_TRY(hipHostMalloc(reinterpret_cast<void **>(&b.staging), n_max * 16, hipHostMallocCoherent));
             HIP_TRY(alloc(&b.d_pts, n_max * 16));
             HIP_TRY(alloc(&b.d_cell, n_max * 4));
             HIP_TRY(alloc(&b.d_slot, n_max * 4));

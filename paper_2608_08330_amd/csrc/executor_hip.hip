@@ -268,18 +268,30 @@ class HipExecutor : public Executor {
         return e;
     }
 
-    // Points of a group of m up to which a kernel on the group's stream reads
-    // them from pinned memory; beyond, a DMA copy per agent.  The kernel saves
-    // the host a copy, an event and a wait per agent and the stream the hand
-    // over from the copy engine, but its reads share the bus with, and hold up,
-    // what runs beside it.  A frame, us, copies -> kernel, points per agent:
-    //   8 alone   24,000 675 -> 680   40,000 697 -> 729   100,000 760 -> 960
-    //   1 alone    8,000 257 -> 252   24,000 261 -> 257    40,000 274 -> 272
-    //   group of 8 8,000 496 -> 412   24,000 506 -> 463    40,000 530 -> 527
-    //   group of 4 8,000 364 -> 321   24,000 371 -> 345    60,000 421 -> 425
-    //   SERIAL, 8  8,000 535 -> 412   24,000 578 -> 464   100,000 808 -> 733
-    static int64_t upload_points(int m, bool serial) {
-        return int64_t(m) * (m == 1 ? 24576 : serial ? 131072 : 40000);
+    // Points in host memory of a group of m (`host` members with such an input)
+    // up to which a kernel on the group's stream reads them from pinned memory;
+    // beyond, a DMA copy per agent.  The kernel saves the host a copy, an event
+    // and a wait per agent and the stream the hand over from the copy engine, but
+    // its reads share the bus with, and hold up, what runs beside it.  A frame of
+    // 100 x 352 cells, us, copies -> kernel, points per agent:
+    //                    4,000        16,000       24,000       40,000       60,000
+    //   1 alone          156 -> 152   160 -> 154   163 -> 158   170 -> 168   180 -> 179
+    //   8 alone          554 -> 556   595 -> 588   598 -> 600   614 -> 620   654 -> 681
+    //     64 x 64 cells  346 -> 339   404 -> 398   421 -> 414   435 -> 461   458 -> 574
+    //     graphs, 6      515 -> 500   526 -> 520   527 -> 525   534 -> 554
+    //     graphs, 8      558 -> 642   596 -> 639   617 -> 653   639 -> 663   697 -> 720
+    //   group of 4       263 -> 222   273 -> 240   276 -> 255   296 -> 287   328 -> 320
+    //   group of 8       391 -> 314   420 -> 353   428 -> 381   448 -> 437   504 -> 496
+    //     graphs         412 -> 340   439 -> 383   444 -> 410   468 -> 466   525 -> 530
+    //   SERIAL, 8 alone  1,005 -> 954 1,011 -> 983 1,025 -> 1,004 1,052 -> 1,079 1,100 -> 1,165
+    //     a group of 4   290 -> 231   309 -> 246   316 -> 260   338 -> 291   366 -> 324
+    // One member's input from the host beside seven on the device: 20,000 points
+    // 310 -> 307, 40,000 326 -> 322, 80,000 358 -> 359, 160,000 432 -> 443.  One of
+    // them large, the others 2,000 points each: 80,000 456 -> 373, 300,000 622 ->
+    // 588 (the sum decides).
+    int64_t upload_points(int m, int host, bool serial) const {
+        const bool queues_full = o_.use_graphs && !serial && p_.K > 6;  // "graphs, 8" above
+        return int64_t(host) * (m == 1 ? (queues_full ? 0 : 24576) : serial ? 131072 : 40000);
     }
 
     rtcc_status dispatch(const DispatchItem *items, int m, std::string &err) override {
@@ -296,9 +308,13 @@ class HipExecutor : public Executor {
         int agents[kern::kMaxGroup];
         kern::PointsUpload up{};  // the inputs that one kernel copies
         int64_t host_pts = 0;
+        int host = 0;
         for (int j = 0; j < m; ++j)
-            if (!items[j].device_src) host_pts += items[j].n;
-        const bool one_upload = !timing && host_pts <= upload_points(m, serial);
+            if (!items[j].device_src && items[j].n > 0) {
+                host_pts += items[j].n;
+                ++host;
+            }
+        const bool one_upload = !timing && host_pts <= upload_points(m, host, serial);
         for (int j = 0; j < m; ++j) {
             const DispatchItem &it = items[j];
             agents[j] = it.agent;

@@ -397,7 +397,7 @@ __host__ __device__ inline int64_t col_base(int c) { return int64_t(64) * c * (c
 // words of a full matrix: 13.3, 19.2 and 119 us.  Quarters for every size
 // would take 17 and 86 us at 1,400 and 4,096 (the footprints are staged four
 // times), whole tiles 30 against 18 us for a frame's 80 crowded boxes.
-constexpr int kQuarterTiles = 64;  // quarters up to this many tiles (11 chunks, 704 candidates)
+constexpr int kQuarterTiles = 64;  // quarters up to this many tiles (10 chunks, 640 candidates)
 __global__ __launch_bounds__(256) void k_nms_mask(NmsArgs a) {
     __shared__ double fr[64 * kFoot], fc[64 * kFoot];
     __shared__ unsigned short list[64 * 64], open[64 * 64];

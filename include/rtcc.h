@@ -421,8 +421,9 @@ RTCC_API rtcc_status rtcc_profile_nodes(rtcc_ctx *ctx, int32_t warmup, int32_t r
                                int32_t *n_nodes);
 
 /* Per-kernel-group GPU durations (ms) of the last frame, recorded when
- * opts.node_timing = 1.  For each agent k, in order: h2d, pillar (cell ids,
- * counting sort, segment), pfn_canvas, conv[0 .. L-1], up[0 .. S-1] (0 if
+ * opts.node_timing = 1.  For each agent k, in order: h2d (from its dispatch
+ * until every input of its group is on the device: copies, or one kernel that
+ * reads them all), pillar (cell ids, counting sort, segment), pfn_canvas, conv[0 .. L-1], up[0 .. S-1] (0 if
  * no upsampling; 0 each when multiscale = 1; where one launch runs all of
  * them, up[0] has its time), warp (0 unless warp_in_branch
  * = 1 and the agent's pose is not the identity, which needs no

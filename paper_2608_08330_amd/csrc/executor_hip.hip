@@ -314,14 +314,16 @@ class HipExecutor : public Executor {
                 host_pts += items[j].n;
                 ++host;
             }
-        const bool one_upload = !timing && host_pts <= upload_points(m, host, serial);
+        const bool one_upload = host_pts <= upload_points(m, host, serial);
         for (int j = 0; j < m; ++j) {
             const DispatchItem &it = items[j];
             agents[j] = it.agent;
             Branch &b = br_[it.agent];
             for (int e = 0; e < 6; ++e) b.affine[e] = it.affine[e];
             hipStream_t bs = serial ? join_stream_ : b.stream;
-            if (timing) HIP_TRY(hipEventRecord(b.ev[0], bs));
+            // (on the member's own stream only where ls waits for its copy)
+            const bool own_copy = !it.device_src && it.n > 0 && !one_upload;
+            if (timing) HIP_TRY(hipEventRecord(b.ev[0], own_copy ? bs : ls));
             const float *src = it.pts;
             if (!it.device_src) {
                 src = static_cast<const float *>(b.d_pts);

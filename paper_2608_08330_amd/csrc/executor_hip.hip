@@ -858,7 +858,7 @@ class HipExecutor : public Executor {
         // Between frames the canvas is zero outside the last frame's pillars
         // (prepare_branch).
         for (int j = 0; j < m; ++j) br_[agents[j]].pillars_clean = false;
-        if (kern::pillars_small_fits(n_cells, grp.n_max, !o_.use_graphs && m < p.K)) {
+        if (kern::pillars_small_fits(n_cells, grp.n_max, m < p.K)) {
             if (clear_ev) HIP_TRY(hipStreamWaitEvent(s, clear_ev, 0));
             HIP_TRY(kern::pillars_small(grp, g, kern::pfn_crowd(p.d.max_points_per_pillar), s));
         } else {

@@ -98,24 +98,25 @@ hipError_t bin_scatter(const PillarGroup &grp, hipStream_t s);
 hipError_t tile_sort(const PillarGroup &grp, int32_t crowd, hipStream_t s);
 // K1 to K3 in one launch, one block per agent, for small inputs: the same
 // lists, member and sorted points.  Two launches fewer, about 10 us of the host
-// where branches are released apart and eagerly, against a kernel that grows
-// with the points and cells of one agent: such releases (host_bound) take it
-// as far as it reaches, a group, a single agent and graphs, whose launches cost
-// the host nothing, up to half of that.  A frame, us, one block -> three
-// launches:
+// where branches are released apart, against a kernel that grows with the
+// points and cells of one agent: such releases take it as far as it reaches, a
+// group and a lone agent, where the stage is all that runs, up to half of that.
+// A frame, us, one block -> three launches:
 //                          points per agent
 //                              2,000        4,000        6,000        8,000
 //   64 x 64, float32, apart, 8 196 -> 215   199 -> 217   200 -> 220   206 -> 219
 //     a group of 8              90 -> 95     94 -> 96     97 -> 97    101 -> 99
 //     a group of 8, graphs     118 -> 115   119 -> 116   122 -> 117   125 -> 119
 //   128 x 128, bf16, apart, 8  305 -> 342   306 -> 345   315 -> 345   328 -> 343
+//     apart, 4, graphs         243 -> 258   244 -> 263   252 -> 258   272 -> 261
 //     a group of 8             132 -> 137   137 -> 139   142 -> 140   147 -> 141
 //     one agent, graphs        116 -> 119   119 -> 120   123 -> 119   128 -> 121
+//   44 x 60, bf16, apart, 4, graphs                      331 -> 341
 //   352 x 100, bf16, apart, 8  513 -> 555   509 -> 544
 //     a group of 8             284 -> 285   287 -> 286
 constexpr int kSmallPoints = 8192, kSmallCells = 16384;
-inline bool pillars_small_fits(int n_cells, int n_max, bool host_bound) {
-    const int points = host_bound ? kSmallPoints : kSmallPoints / 2;
+inline bool pillars_small_fits(int n_cells, int n_max, bool apart) {
+    const int points = apart ? kSmallPoints : kSmallPoints / 2;
     return n_cells <= kSmallCells ? n_max <= points : n_cells <= kSmallCells * 4 && n_max <= points / 2;
 }
 hipError_t pillars_small(const PillarGroup &grp, const PillarGeom &g, int32_t crowd, hipStream_t s);

@@ -45,12 +45,12 @@ PEAK_HBM_GBS = 8000.0       # MI355X HBM3E
 MEASURED_TRAFFIC = {
     # per 8-agent launch of a conv layer (averaged over the 13 layers)
     "conv": dict(src="paper_2608_08330_amd/csrc/kernels/igemm.hip", bytes=154.8e6,
-                 sha256="1ea11a11e3bed1bdddb119fe33f47298bae88df767b509db8774190339f217c4"),
+                 sha256="282619bdaaeee5630b56ef8d286468002bfbd01632ddd5f7c98f9e7834d21d85"),
     "warp_fuse": dict(src="paper_2608_08330_amd/csrc/kernels/post.hip", bytes=472.6e6,
                       sha256="5c1888d1dbf57d48630d258a3585463140bf07b822625e3af4468009cc6f2cb1"),
     # per 8-agent launch chain of the pillar stage (four kernels)
     "pillar": dict(src="paper_2608_08330_amd/csrc/kernels/pillar.hip", bytes=189e6,
-                   sha256="f7137703c01e3ac69881b4077f6507e610af285f23167e354f9af9b00b265186"),
+                   sha256="a7a5915926c503c2019bbcb549556e2280164571f4451d634b215fe902994a4d"),
 }
 
 
@@ -556,7 +556,7 @@ def main(argv=None):
             "pillar_alone": round(float(np.mean([node_1[:, k * per_agent + 1] for k in range(K)])), 4),
             "pfn_canvas_alone": round(float(np.mean([node_1[:, k * per_agent + 2] for k in range(K)])), 4),
             "conv_total_per_agent": round(conv_ms / (K * rsteps), 4),
-            "up_total_per_agent": round(float(np.sum([node[:, k * per_agent + 3 + L:k * per_agent + per_agent]
+            "up_total_per_agent": round(float(np.sum([node[:, k * per_agent + 3 + L:k * per_agent + 3 + L + S]
                                                       for k in range(K)]) / (K * rsteps)), 4),
             "branch_warp_per_agent": round(bw_ms / (K * rsteps), 4),
             ("multiscale_fusion_upsample" if cfg["multiscale"] else "fuse" if cfg["warp_in_branch"]

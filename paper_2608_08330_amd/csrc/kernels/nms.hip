@@ -28,10 +28,10 @@
 //                  with a non-finite parameter or w <= 0 or l <= 0 overlaps
 //                  nothing.
 //   k_nms_select   the greedy selection as the fixed point of "kept = no kept
-//                  suppressor ranked before", every 64-row chunk at once: a
-//                  chunk takes the rows removed by the listed words of kept
-//                  rows and resolves itself; after t rounds the first t
-//                  chunks are final, and a few rounds suffice in practice.
+//                  suppressor ranked before", a window of 64-row chunks at
+//                  once: a chunk takes the rows removed by the listed words of
+//                  kept rows and resolves itself; the window moves behind the
+//                  first chunk that a round changes.
 //                  The kept records are then compacted in ascending record
 //                  (anchor) order and, at the end of a join, also written to
 //                  the host.

@@ -26,9 +26,12 @@ ConvPlan conv_plan(bool bf16, int Hi, int Wi, int Ci, int Ho, int Wo, int Co, in
     // Many maps fill the chip: a block of conv_slices reads its weights for 32 or
     // 64 pixels only, so from 128 input channels with stride 2, and from 256 with
     // stride 1, a launch takes the halo tilings from halo_maps maps on, which then
-    // sum the same slices (3 to 6% slower than without, from the extra sums).  The
-    // lines, in 4 x 16 x 128 tiles over all maps, are half the CUs for 512-byte
-    // pixels with stride 2, three quarters for 256-byte ones, all for stride 1.
+    // sum the same slices (3 to 6% slower than without, from the extra sums): with
+    // more 4 x 16 x 128 tiles over all maps than half the CUs for 512-byte pixels
+    // with stride 2, 7 / 8 of them for 256-byte ones, all for stride 1 (a little
+    // late for a layer by itself; inside a network, its input still in the L2,
+    // 192 tiles of 32 x 32 x 256 at stride 2 take 11.5 -> 12.1, and a frame with
+    // eight 32 x 32 x 256 maps, 256 tiles, 384 -> 390).
     // us, slices -> halo tilings, over the maps:
     //   50 x 88 x 256 -> 25 x 44 x 256   3: 18.1 -> 19.6   4: 25.3 -> 20.2   8: 40.8 -> 30.2 (without slices 30.1)
     //   128 x 128 x 128 -> 64 x 64 x 128 2: 10.1 -> 13.0   3: 14.3 -> 13.8   8: 28.5 -> 20.8 (20.0)
@@ -69,8 +72,8 @@ ConvPlan conv_plan(bool bf16, int Hi, int Wi, int Ci, int Ho, int Wo, int Co, in
                 const int t8 = ((Wo + 15) / 16) * ((Ho + 7) / 8) * (Co / 128);
                 p.variant_wide = p.variant_wider = stride == 1 ? kConvHalo8 : kConvHalo8S2;
                 p.wide_maps = (n_cu + t8 - 1) / t8;
-                if (Ci * elt == 512) p.halo_maps = stride == 1 ? (n_cu + t4 - 1) / t4 : n_cu / 2 / t4 + 1;
-                else if (Ci * elt == 256 && stride == 2) p.halo_maps = (n_cu * 3 / 4 + t4 - 1) / t4;
+                if (Ci * elt == 512) p.halo_maps = (stride == 1 ? n_cu : n_cu / 2) / t4 + 1;
+                else if (Ci * elt == 256 && stride == 2) p.halo_maps = n_cu * 7 / 8 / t4 + 1;
             }
             return p;
         }

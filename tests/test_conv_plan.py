@@ -143,9 +143,10 @@ def planner(tmp_path_factory):
     # from 256: up to 32 channels, or below 5 tiles per 8 CUs
     ((True, 256, 2000, 2000, 32, 2), (4, None)), ((True, 256, 79, 128, 96, 2), (4, None)),
     ((True, 256, 80, 128, 96, 2), (0, None)), ((True, 256, 80, 128, 64, 2), (4, None)),
-    # the maps from which the halo tilings run: 256 tiles, 129, 192
-    ((True, 256, 64, 64, 128, 1), (4, 4)), ((True, 256, 64, 60, 128, 2), (4, 3)), ((True, 256, 60, 64, 128, 2), (4, 3)),
-    ((True, 128, 64, 64, 128, 2), (4, 3)), ((True, 128, 60, 64, 128, 2), (4, 4)), ((True, 128, 64, 64, 128, 1), (4, None)),
+    # the maps from which the halo tilings run: more than 256 tiles, 128, 224
+    ((True, 256, 64, 64, 128, 1), (4, 5)), ((True, 256, 64, 68, 128, 1), (4, 4)),
+    ((True, 256, 64, 64, 128, 2), (4, 3)), ((True, 256, 64, 68, 128, 2), (4, 2)),
+    ((True, 128, 56, 64, 128, 2), (4, 5)), ((True, 128, 60, 64, 128, 2), (4, 4)), ((True, 128, 64, 64, 128, 1), (4, None)),
 ])
 def test_where_slices_are_summed_side_by_side(planner, shape, want):
     assert planner(*shape) == want

@@ -227,37 +227,33 @@ hipError_t upsample_frag(const void *wt, void *out, int32_t u, int32_t Co, int32
 }
 
 hipError_t upsample(UpsampleArgs a, hipStream_t s) {
-    // One group per block and P = 1, for the shortest chain, while the blocks are
-    // not many times what runs at once; from there on P = 2 and more groups per
-    // block, whose pixels are staged once for all of them: every group of the
-    // pixel at u = 1, two of a larger kernel's, and four once the blocks are many
-    // more.  A single group per pixel (one stage, u = 1, 128 channels) has
-    // nothing to share.  And P = 2 where its blocks, four per CU, run all at once
-    // and those of P = 1, three per CU, do not.  us, over the blocks of one group,
-    // P = 1 -> P = 2 (groups per block):
+    // One group per block and P = 1, for the shortest chain, until the blocks are
+    // many times what runs at once; then four groups, so that the pixels are
+    // staged for four phases, and P = 2.  One stage by itself (u = 1) takes all
+    // groups of its pixels, and P = 2, from 2,560 blocks on; several stages, whose
+    // blocks share a CU, gain less in a network than alone (eight maps of 128 x 128
+    // with two groups per block 52.5 -> 50.4 alone, a frame 384 -> 386).  And P = 2
+    // where its blocks, four per CU, run all at once and those of P = 1, three per
+    // CU, do not.  us, over the blocks of one group, P = 1 -> P = 2 (groups per
+    // block):
     //   one stage, 256 -> 128    825  17.3 -> 15.3 (1)    1,024 20.1 -> 17.3 (1)    2,048 32.4 -> 34.8 (1)
     //   one stage, 256 -> 256  4,096  50.1 -> 45.5 (2)    6,144 65.5 -> 62.2 (2)
     //   one stage, 256 -> 384    768  12.9 -> 16.2 (2)    3,072 39.6 -> 28.4 (3)    6,144 69.9 -> 60.5 (3)
-    //   64 / 128 / 256 -> 128  1,768  27.9 -> 29.4 (2)    3,072 39.4 -> 37.0 (2)    9,216 81.6 -> 73.0 (2)
-    //                         24,576 189.5 -> 158.3 (2), 153.0 (4)
-    //   64 / 128 -> 256        2,256  23.5 -> 23.1 (2)    8,192 52.8 -> 47.2 (2)    12,288 74.3 -> 61.0 (2)
+    //   64 / 128 / 256 -> 128 24,576 189.5 -> 153.0 (4)
     int64_t single = 0;
-    bool shared = false;
     for (int q = 0; q < a.n_stages; ++q) {
         const UpsampleStage &st = a.stage[q];
         if (!upsample_fits(true, st.Ci, a.Co)) return hipErrorInvalidValue;
-        const int groups = st.u * st.u * (a.Co >> 7);
-        single += int64_t((st.Hi * st.Wi + kPx - 1) / kPx) * groups;
-        shared = shared || groups > 1;
+        single += int64_t((st.Hi * st.Wi + kPx - 1) / kPx) * st.u * st.u * (a.Co >> 7);
     }
     single *= a.batch;
-    const bool many = single > 14336, some = shared && single > 2560;
-    const bool two = many || some || (single > 768 && single <= 1024);
+    const bool many = single > 14336 || (a.n_stages == 1 && a.Co > 128 && single > 2560);
+    const bool two = many || (single > 768 && single <= 1024);
+    const int per = many ? 4 : 1;
     int64_t blocks = 0;
     for (int q = 0; q < a.n_stages; ++q) {
         UpsampleStage &st = a.stage[q];
         const int groups = st.u * st.u * (a.Co >> 7);
-        const int per = many || (some && st.u == 1) ? 4 : some ? 2 : 1;
         st.per = per < groups ? per : groups;
         st.blocks = (st.Hi * st.Wi + kPx - 1) / kPx * ((groups + st.per - 1) / st.per);
         st.run = int32_t((int64_t(st.blocks) * a.batch + 7) / 8);

@@ -30,10 +30,10 @@ SHAPES = [
     ("wide_up", "bf16", 64, ((2, 128, 1), (2, 256, 1)), 256, (30, 46)),      # two blocks of 128 output channels
     # eight maps: more blocks than the one-group upsampling takes, 64 / 128 / 256 input channels
     ("many_up", "bf16", 64, ((1, 64, 1), (2, 128, 1), (2, 256, 1)), 128, (197, 203)),
-    # ... and two blocks of 128 output channels; eight maps: two groups per block, four
+    # ... and two blocks of 128 output channels; eight maps: one group per block, four
     ("some_wide_up", "bf16", 64, ((1, 64, 1), (2, 256, 1)), 256, (150, 170)),
     ("many_wide_up", "bf16", 64, ((1, 64, 1), (2, 256, 1)), 256, (170, 190)),
-    # one map: 888 blocks, which run at once by twos; eight: the three groups of a pixel in one block
+    # one map: 888 blocks, which run all at once with two wavefronts each; eight: the three groups of a pixel in one block
     ("up_384", "bf16", 64, ((1, 64, 1),), 384, (135, 140)),
     ("fp32", "fp32", 64, ((2, 32, 2),), 32, (47, 95)),
     # group launches by the halo tilings: 8 rows of 16 pixels, strides 1 and 2 ...

@@ -26,7 +26,7 @@ ConvPlan conv_plan(bool bf16, int Hi, int Wi, int Ci, int Ho, int Wo, int Co, in
     // Many maps fill the chip: a block of conv_slices reads its weights for 32 or
     // 64 pixels only, so from 128 input channels with stride 2, and from 256 with
     // stride 1, a launch takes the halo tilings from halo_maps maps on, which then
-    // sum the same slices (3 to 6% slower than without, from the extra sums): with
+    // sum the same slices (3 to 10% slower than without, from the extra sums): with
     // more 4 x 16 x 128 tiles over all maps than half the CUs for 512-byte pixels
     // with stride 2, 7 / 8 of them for 256-byte ones, all for stride 1 (a little
     // late for a layer by itself; inside a network, its input still in the L2,
